@@ -48,7 +48,7 @@ struct HistArgs {
   int32_t shift;  // 8 - log2(B): bin = v >> shift
   int32_t logB;
   int32_t splits; // workgroups per frame
-  int32_t units;  // whole 768-byte units covered by the vector path
+  int32_t units;  // whole 768-byte units of a frame covered by the vector path
   int32_t atomic; // 1: several workgroups per frame add into a zeroed histogram
   // frame t of the launch reads frame (t / group) * in_stride + in_off + t % group
   // and writes histogram row (t / group) * out_stride + out_off + t % group;
@@ -143,6 +143,13 @@ __device__ __forceinline__ void count_pixel(uint32_t* cnt, const uint8_t* px, ui
 __host__ __device__ __forceinline__ int64_t hist_map(int64_t t, int64_t group, int64_t stride, int64_t off) {
   return group ? (t / group) * stride + off + t % group : t;
 }
+// Pixels (of C bytes) at the start of a frame that the byte path counts so
+// that the vector path's 4-byte loads behind them are aligned and begin at a
+// pixel: with 3-byte pixels, skipping h moves the address by 3 h = -h mod 4.
+// At most 3; 0 for a 4-byte aligned frame.
+__host__ __device__ __forceinline__ int hist_head(uintptr_t frame_addr, int C) {
+  return C == 3 ? (int)(frame_addr & 3) : (int)((4 - (frame_addr & 3)) & 3);
+}
 // Unit that wave g (of G sharing a frame) loads as the i-th of its batches'
 // units: g + i G, clamped to the last whole unit.
 __host__ __device__ __forceinline__ int hist_unit(int g, int i, int G, int units) {
@@ -161,7 +168,13 @@ __global__ __launch_bounds__(512) void ngff_hist_kernel(HistArgs a) {
   const int s = (int)(blockIdx.x - t * a.splits);
   const int64_t src_frame = hist_map(t, a.group, a.in_stride, a.in_off);
   const int64_t dst_row = hist_map(t, a.group, a.out_stride, a.out_off);
+  constexpr int C = (KIND == K_GRAY1) ? 1 : 3;
   const uint8_t* f = a.frames + src_frame * a.frame_bytes;
+  // a frame that starts at any byte: its first `head` pixels go with the tail
+  // (a call over 300 frames of 719 x 1279, each of which used to take the
+  // byte path whole: 1540 -> 208 us)
+  const int head = a.units > 0 ? hist_head(reinterpret_cast<uintptr_t>(f), C) : 0;
+  const uint8_t* fv = f + head * C;
   const int G = a.splits * nw;  // waves sharing this frame
   const int g = s * nw + wave;
   // batches of kUnroll units per wave (unit u0 + j G), software pipelined: the
@@ -175,7 +188,7 @@ __global__ __launch_bounds__(512) void ngff_hist_kernel(HistArgs a) {
       const int u = hist_unit(g, b * kUnroll + j, G, a.units);
       // frames are read once: non-temporal loads (1 fps stream 28.0 -> 26.4 us,
       // high-res 1031 -> 938 us)
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(f + (int64_t)u * kUnitBytes + lane * 12);
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(fv + (int64_t)u * kUnitBytes + lane * 12);
       v[j].x = __builtin_nontemporal_load(src);
       v[j].y = __builtin_nontemporal_load(src + 1);
       v[j].z = __builtin_nontemporal_load(src + 2);
@@ -205,11 +218,10 @@ __global__ __launch_bounds__(512) void ngff_hist_kernel(HistArgs a) {
     }
     if (b < nbatch) count_batch(va, b);
   }
-  // pixels after the whole units (or every pixel of an unaligned frame)
-  const int C = (KIND == K_GRAY1) ? 1 : 3;
-  const int64_t p0 = (int64_t)a.units * (kUnitBytes / C);
-  for (int64_t p = p0 + (int64_t)g * 64 + lane; p < a.npix; p += (int64_t)G * 64)
-    count_pixel<KIND, P, BC>(cnt, f + p * C, lane, a);
+  // pixels outside the whole units: after them, and the head
+  const int64_t mid = (int64_t)a.units * (kUnitBytes / C);  // pixels of the units
+  for (int64_t q = (int64_t)g * 64 + lane; q < a.npix - mid; q += (int64_t)G * 64)
+    count_pixel<KIND, P, BC>(cnt, f + (q < head ? q : q + mid) * C, lane, a);
   __syncthreads();
 
   // merge the P lane copies: J threads per bin each add P/J copies (rotated by
@@ -1070,9 +1082,11 @@ HistPlan plan_hist(const NgffShape& sh, const uint8_t* frames) {
   // batches (1 fps stream 28.7 vs 32.2 us, hour stream 385 vs 458 us), more
   // bytes in flight per CU did not stream faster
   p.threads = 512;
-  // the vector path needs 4-byte aligned frames
+  // where frames start at any byte, the vector path begins up to 3 pixels
+  // into each frame (hist_head) and every frame has the same whole units left
   const bool aligned = (reinterpret_cast<uintptr_t>(frames) % 4 == 0) && (sh.frame_bytes % 4 == 0);
-  p.units = aligned ? (int)(sh.frame_bytes / kUnitBytes) : 0;
+  const int64_t head = aligned ? 0 : 3 * sh.C;
+  p.units = sh.frame_bytes > head ? (int)((sh.frame_bytes - head) / kUnitBytes) : 0;
   const int nw = p.threads / 64;
   // one workgroup per frame when there are at least as many frames as CUs,
   // otherwise split frames so that every CU streams
@@ -1101,15 +1115,21 @@ void model_hist(const HistArgs& a, int64_t n, int threads, size_t lds) {
   dry_lds(0, (int64_t)a.nbins * P * 4, (int64_t)lds, "hist: counters");
   for (int64_t t = 0; t < n; ++t) {
     const int64_t fb = hist_map(t, a.group, a.in_stride, a.in_off) * a.frame_bytes;
+    const uintptr_t fa = reinterpret_cast<uintptr_t>(a.frames) + (uintptr_t)fb;
+    const int head = a.units > 0 ? hist_head(fa, C) : 0;
+    const int64_t fv = fb + (int64_t)head * C;
+    if (a.units > 0) dry_range((int64_t)((fa + (uintptr_t)(head * C)) & 3), 0, 1, "hist: unit loads of 4-byte words");
     for (int g = 0; g < G; ++g) {
       const int nbatch = g < a.units ? (a.units - g + G * kUnroll - 1) / (G * kUnroll) : 0;
       const int last_b = nbatch > 0 ? 2 * (nbatch / 2) : -1;  // the pipeline loads one batch past an even count
       for (int b = 0; b <= last_b; ++b)
         for (int j = 0; j < kUnroll; ++j)
-          dry_access(a.frames, fb + (int64_t)hist_unit(g, b * kUnroll + j, G, a.units) * kUnitBytes, kUnitBytes,
+          dry_access(a.frames, fv + (int64_t)hist_unit(g, b * kUnroll + j, G, a.units) * kUnitBytes, kUnitBytes,
                      "hist: unit load");
     }
-    const int64_t p0 = (int64_t)a.units * (kUnitBytes / C);
+    const int64_t p0 = head + (int64_t)a.units * (kUnitBytes / C);
+    dry_range(p0, 0, a.npix + 1, "hist: head and units past the pixels");
+    if (head > 0) dry_access(a.frames, fb, (int64_t)head * C, "hist: pixels before the units");
     if (p0 < a.npix) dry_access(a.frames, fb + p0 * C, (a.npix - p0) * C, "hist: pixels after the units");
     dry_access(a.hist, hist_map(t, a.group, a.out_stride, a.out_off) * a.nbins * 4, (int64_t)a.nbins * 4,
                "hist: histogram row");

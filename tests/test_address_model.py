@@ -376,7 +376,8 @@ def test_ngff_shapes(shape, mode, bins):
     n, H, W, C = shape
     with B.DryRun() as dr:
         ngff_filter(dr, n, H, W, C, mode, bins)
-        ngff_filter(dr, n, H, W, C, mode, bins, misalign=1)  # byte path of a frame at an odd address
+        for m in (1, 2, 3):  # frames that start at any byte
+            ngff_filter(dr, n, H, W, C, mode, bins, misalign=m)
         clean(dr, "NGFF shapes")
 
 

@@ -53,6 +53,26 @@ def test_histogram_gray_single_channel(shape, bins):
     assert np.array_equal(gpu_hist(f, bins, "gray"), oracle.histogram(f, bins, oracle.GRAY))
 
 
+@pytest.mark.parametrize("H,W", [(17, 53),    # just past one unit (a head of 3 pixels leaves one)
+                                 (16, 16),    # one unit exactly: none when the frame may start at any byte
+                                 (121, 135)])  # several batches of units, every alignment among the frames
+@pytest.mark.parametrize("mode,bins", [("per_channel", 32), ("joint3d", 8), ("gray", 32), ("gray1", 32)])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_histogram_frames_at_any_byte(H, W, mode, bins, offset):
+    """Frames whose addresses take every remainder mod 4: the pixels before the
+    first aligned one, the vector units and the tail together count each pixel
+    once."""
+    C = 1 if mode == "gray1" else 3
+    mode = "gray" if mode == "gray1" else mode
+    n = 5
+    f = synth.random_frames(11 + offset, n, H, W, C=C)
+    buf = torch.zeros(f.size + 8, dtype=torch.uint8, device="cuda")
+    view = buf[offset:offset + f.size].view(f.shape)
+    view.copy_(to_dev(f))
+    got = hist_np(B.cofie_ngff_histogram(view if C == 3 else view[..., 0], bins, mode))
+    assert np.array_equal(got, oracle.histogram(f if C == 3 else f[..., 0], bins, MODES[mode]))
+
+
 def test_histogram_extreme_values():
     """All-0 and all-255 frames, and every byte value, land in the edge bins."""
     f = np.zeros((3, 16, 48, 3), dtype=np.uint8)
