@@ -262,96 +262,177 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, int64_t count) {
 // the frame difference emits the gh gw means, dHash the 64 bits "cell
 // (r, c+1) brighter than cell (r, c)" of an 8 x 9 grid.  The rows' L1 distance
 // over 255 gh gw (or 64) is the signal's distance, so the keep rule runs on
-// them like on histogram rows.  One workgroup per frame: each wave takes whole
-// image rows, each lane 4 consecutive pixels per load (12 contiguous bytes:
-// 768 per wave instruction when the frame allows it), sums a run of pixels of
-// one cell in registers and adds it to the cell's LDS counter.
+// them like on histogram rows.
+//
+// A grid row's cells depend on its own image rows only, so a workgroup takes
+// bpw whole grid rows of a frame and finishes them: many small workgroups per
+// frame, no hand-off between them.  Its work is cut into tasks of one group of
+// 4 pixel columns over one of `sub` slices (at most 16 rows) of a grid row's
+// image rows, dealt to the lanes in order, so consecutive lanes read
+// consecutive 12 bytes of a row whatever the width (only a row's last group,
+// which begins at column W - 4 and drops the columns the group before it has,
+// reads a byte twice).  A lane keeps its 4 columns' sums in registers over the
+// task's rows and adds them to the cells once, at the task's end: per 12 bytes
+// about 30 VALU operations (two 4-byte dot products, a shift-add and one
+// 24-bit multiply a luma) and 1/16 of the LDS additions of one per row.  Rows
+// start at any byte: the loads are byte-aligned dwords.  600 frames of
+// 480 x 853, frame difference, whole filter call: 1001 us with one workgroup
+// of 4 waves per frame, byte loads and an LDS addition a pixel; 228 us here.
 struct SigArgs {
   const uint8_t* frames;
   int64_t frame_bytes;
   int32_t H, W, C;
-  int32_t gh, gw;
-  int32_t dhash;  // 1: the 64 hash bits, 0: the gh gw cell means
+  int32_t gh, gw;  // gh a power of two
+  int32_t lgh;     // log2 gh
+  int32_t dhash;   // 1: the 64 hash bits, 0: the gh gw cell means
   int32_t nsig;
-  int32_t vec;    // 1: 4-pixel loads (4-byte aligned frames, W a multiple of 4)
-  uint32_t* out;  // [n][nsig]
+  int32_t parts;   // workgroups per frame
+  int32_t bpw;     // grid rows per workgroup (parts * bpw >= gh)
+  int32_t sub;     // row slices per grid row
+  int32_t slice;   // image rows per slice
+  int32_t groups;  // column groups per row
+  uint32_t* out;   // [n][nsig]
 };
 
 constexpr int kSigThreads = 256;
 constexpr int kSigMaxW = 16384;  // the column -> grid column table (uint16, LDS)
 
+// First image row of grid row i of 2^lg, first image column of grid column i of g.
+__host__ __device__ __forceinline__ int sig_first_row(int i, int H, int lg) {
+  return (int)(((int64_t)i * H + (1 << lg) - 1) >> lg);
+}
+__host__ __device__ __forceinline__ int sig_first_col(int i, int W, int g) { return (int)((uint32_t)(i * W + g - 1) / (uint32_t)g); }
+// Task e of a workgroup whose first grid row is b0: its grid row, its image
+// rows [ya, yb), its first column x0 and the column xb its loads begin at
+// (4 columns inside the row; W < 4 reads byte by byte from column 0).
+struct SigTask {
+  int band, ya, yb, x0, xb;
+};
+__host__ __device__ __forceinline__ SigTask sig_task(const SigArgs& a, int e, int b0) {
+  const int W = a.W;
+  const int rb = (int)((uint32_t)e / (uint32_t)a.groups), j = e - rb * a.groups;
+  const int band = (int)((uint32_t)rb / (uint32_t)a.sub), sl = rb - band * a.sub;
+  const int hi = sig_first_row(b0 + band + 1, a.H, a.lgh);
+  SigTask t;
+  t.band = band;
+  t.ya = sig_first_row(b0 + band, a.H, a.lgh) + sl * a.slice;
+  t.yb = t.ya + a.slice < hi ? t.ya + a.slice : hi;
+  t.x0 = 4 * j;
+  t.xb = t.x0 + 4 <= W ? t.x0 : (W >= 4 ? W - 4 : 0);
+  return t;
+}
+
+// luma_bt601 of the pixel in bytes 0..2 of px (byte 3 is ignored).  The
+// weights in bytes: 299, 587, 114 = 256 (1, 2, 0) + (43, 75, 114).  x / 1000
+// for x <= 255500 as the high half of x ceil(2^32 / 1000): the multiplier is
+// 0.704 above 2^32 / 1000, an error below 255500 * 0.704 / 2^32 < 1 / 1000.
+__device__ __forceinline__ uint32_t luma_dot(uint32_t px) {
+  const uint32_t lo = __builtin_amdgcn_udot4(px, 43u | (75u << 8) | (114u << 16), 500u, false);
+  const uint32_t hi = __builtin_amdgcn_udot4(px, 1u | (2u << 8), 0u, false);
+  const uint32_t x = (hi << 8) + lo;
+  return (uint32_t)(((uint64_t)(x & 0xFFFFFFu) * (uint64_t)4294968u) >> 32);
+}
+
+typedef uint32_t u32_any __attribute__((aligned(1)));  // a dword at any byte
+
+// The 4 pixels at p as raw words: 12 bytes of RGB or 4 of gray.
+template <int C>
+struct SigPx {
+  uint32_t w[C];
+};
+
+template <int C, bool NARROW, int UN>
 __global__ __launch_bounds__(kSigThreads) void ngff_sig_kernel(SigArgs a) {
-  __shared__ uint32_t cell[4096];
-  __shared__ uint16_t gcol[kSigMaxW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = kSigThreads / 64;
-  const int ncell = a.gh * a.gw;
-  for (int i = tid; i < ncell; i += kSigThreads) cell[i] = 0;
-  for (int x = tid; x < a.W; x += kSigThreads) gcol[x] = (uint16_t)(((int64_t)x * a.gw) / a.W);
+  extern __shared__ uint32_t cell[];  // [bpw][gw], then the column table [W] (uint16)
+  uint16_t* gcol = reinterpret_cast<uint16_t*>(cell + a.bpw * a.gw);
+  const int tid = threadIdx.x;
+  const int64_t frame = blockIdx.x / a.parts;
+  const int b0 = (int)(blockIdx.x - frame * a.parts) * a.bpw;
+  const int nb = a.gh - b0 < a.bpw ? a.gh - b0 : a.bpw;
+  if (nb <= 0) return;
+  for (int i = tid; i < nb * a.gw; i += kSigThreads) cell[i] = 0;
+  for (int x = tid; x < a.W; x += kSigThreads) gcol[x] = (uint16_t)((uint32_t)(x * a.gw) / (uint32_t)a.W);
   __syncthreads();
-  const uint8_t* f = a.frames + (int64_t)blockIdx.x * a.frame_bytes;
-  auto luma = [&](uint32_t r, uint32_t g, uint32_t b) __attribute__((always_inline)) {
-    return a.C == 3 ? luma_bt601(r, g, b) : r;
-  };
-  for (int y = wave; y < a.H; y += nw) {
-    const int cy = (int)(((int64_t)y * a.gh) / a.H) * a.gw;
-    const uint8_t* row = f + (int64_t)y * a.W * a.C;
-    if (a.vec) {
-      // lane: pixels x0 .. x0 + 3 (12 bytes of RGB or 4 bytes of gray)
-      for (int x0 = 4 * lane; x0 < a.W; x0 += 256) {
-        uint32_t v[4];
-        if (a.C == 3) {
-          const U3 w = *reinterpret_cast<const U3*>(row + 3 * x0);
-          v[0] = luma(w.x & 255u, (w.x >> 8) & 255u, (w.x >> 16) & 255u);
-          v[1] = luma(w.x >> 24, w.y & 255u, (w.y >> 8) & 255u);
-          v[2] = luma((w.y >> 16) & 255u, w.y >> 24, w.z & 255u);
-          v[3] = luma((w.z >> 8) & 255u, (w.z >> 16) & 255u, w.z >> 24);
-        } else {
-          const uint32_t w = *reinterpret_cast<const uint32_t*>(row + x0);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = (w >> (8 * i)) & 255u;
+  const uint8_t* f = a.frames + frame * a.frame_bytes;
+  const int64_t row_bytes = (int64_t)a.W * C;
+  const int tasks = nb * a.sub * a.groups;
+  for (int e = tid; e < tasks; e += kSigThreads) {
+    const SigTask t = sig_task(a, e, b0);
+    const uint8_t* p = f + (int64_t)t.ya * row_bytes + t.xb * C;
+    const int rows = t.yb - t.ya;
+    uint32_t s[4] = {0u, 0u, 0u, 0u};
+    if constexpr (NARROW) {
+      for (int y = 0; y < rows; ++y)
+        for (int i = 0; i < a.W; ++i) {
+          const uint8_t* px = p + y * row_bytes + i * C;
+          s[i & 3] += C == 3 ? luma_bt601(px[0], px[1], px[2]) : px[0];
         }
-        // runs of one cell: one LDS add per run
-        int c = gcol[x0];
-        uint32_t run = v[0];
-#pragma unroll
-        for (int i = 1; i < 4; ++i) {
-          const int ci = gcol[x0 + i];
-          if (ci != c) {
-            atomicAdd(&cell[cy + c], run);
-            c = ci;
-            run = 0;
-          }
-          run += v[i];
-        }
-        atomicAdd(&cell[cy + c], run);
-      }
     } else {
-      for (int x = lane; x < a.W; x += 64) {
-        const uint8_t* px = row + (int64_t)x * a.C;
-        const uint32_t v = a.C == 3 ? luma_bt601(px[0], px[1], px[2]) : px[0];
-        atomicAdd(&cell[cy + gcol[x]], v);
+      for (int y0 = 0; y0 < rows; y0 += UN) {
+        SigPx<C> v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {  // rows past the task's repeat its last and are not added
+          const int y = y0 + u < rows ? y0 + u : rows - 1;
+          const u32_any* q = reinterpret_cast<const u32_any*>(p + y * row_bytes);
+#pragma unroll
+          for (int i = 0; i < C; ++i) v[u].w[i] = __builtin_nontemporal_load(q + i);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          uint32_t l[4];
+          if constexpr (C == 3) {
+            const uint32_t w0 = v[u].w[0], w1 = v[u].w[1], w2 = v[u].w[2];
+            l[0] = luma_dot(w0);
+            l[1] = luma_dot(__builtin_amdgcn_alignbyte(w1, w0, 3));
+            l[2] = luma_dot(__builtin_amdgcn_alignbyte(w2, w1, 2));
+            l[3] = luma_dot(w2 >> 8);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l[i] = (v[u].w[0] >> (8 * i)) & 255u;
+          }
+          const bool in = y0 + u < rows;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[i] += in ? l[i] : 0u;
+        }
       }
     }
+    // the columns x0 .. of the group: one LDS addition per run of one cell
+    uint32_t* cr = cell + t.band * a.gw;
+    int c = -1;
+    uint32_t run = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int x = t.xb + i;
+      if (x >= t.x0 && x < a.W) {
+        const int ci = gcol[x];
+        if (ci != c) {
+          if (c >= 0) atomicAdd(cr + c, run);
+          c = ci;
+          run = 0;
+        }
+        run += s[i];
+      }
+    }
+    if (c >= 0) atomicAdd(cr + c, run);
   }
   __syncthreads();
   // cell means, rounded half up: grid row i spans rows [ceil(i H / gh),
   // ceil((i + 1) H / gh)), grid column j likewise
-  auto first = [](int64_t i, int64_t len, int64_t g) __attribute__((always_inline)) { return (i * len + g - 1) / g; };
-  for (int i = tid; i < ncell; i += kSigThreads) {
+  uint32_t* o = a.out + frame * a.nsig;
+  for (int i = tid; i < nb * a.gw; i += kSigThreads) {
     const int r = i / a.gw, c = i - r * a.gw;
-    const uint32_t area = (uint32_t)((first(r + 1, a.H, a.gh) - first(r, a.H, a.gh)) *
-                                     (first(c + 1, a.W, a.gw) - first(c, a.W, a.gw)));
-    cell[i] = (cell[i] + area / 2) / area;
+    const uint32_t area = (uint32_t)((sig_first_row(b0 + r + 1, a.H, a.lgh) - sig_first_row(b0 + r, a.H, a.lgh)) *
+                                     (sig_first_col(c + 1, a.W, a.gw) - sig_first_col(c, a.W, a.gw)));
+    const uint32_t mean = (cell[i] + area / 2) / area;
+    if (a.dhash) cell[i] = mean;
+    else o[b0 * a.gw + i] = mean;
   }
-  __syncthreads();
-  uint32_t* o = a.out + (int64_t)blockIdx.x * a.nsig;
   if (a.dhash) {
-    if (tid < 64) {
-      const int r = tid >> 3, c = tid & 7;
-      o[tid] = cell[r * 9 + c + 1] > cell[r * 9 + c] ? 1u : 0u;
+    __syncthreads();
+    for (int i = tid; i < 8 * nb; i += kSigThreads) {
+      const int r = i >> 3, c = i & 7;
+      o[8 * b0 + i] = cell[r * 9 + c + 1] > cell[r * 9 + c] ? 1u : 0u;
     }
-  } else {
-    for (int i = tid; i < ncell; i += kSigThreads) o[i] = cell[i];
   }
 }
 
@@ -1171,29 +1252,40 @@ struct HistMap {  // see HistArgs: group = 0 is the identity
   bool zeroed = false;   // the output rows are known zero: no fill before accumulating
 };
 
-// Address model of ngff_sig_kernel (dry run): each frame's rows as the
-// vector or byte path reads them, the LDS column table and cell counters,
-// the output row.
-void model_sig(const SigArgs& a, int64_t n) {
+// Address model of ngff_sig_kernel (dry run): every task's rows as its loads
+// read them, the LDS column table and cell counters, the output rows.  Every
+// pixel belongs to exactly one task's columns.
+void model_sig(const SigArgs& a, int64_t n, bool narrow, size_t lds) {
   dry_range(a.W, 1, kSigMaxW + 1, "sig: columns past the column table");
-  dry_range((int64_t)a.gh * a.gw, 1, 4097, "sig: cells past the counters");
   dry_range((int64_t)a.H * a.W * a.C, 1, a.frame_bytes + 1, "sig: pixels past the frame");
-  const int64_t top_cell = (int64_t)((((int64_t)(a.H - 1) * a.gh) / a.H) * a.gw) + ((int64_t)(a.W - 1) * a.gw) / a.W;
-  dry_range(top_cell, 0, (int64_t)a.gh * a.gw, "sig: a pixel's cell");
-  for (int64_t b = 0; b < n; ++b) {
-    const int64_t f = b * a.frame_bytes;
-    const int64_t last_row = f + (int64_t)(a.H - 1) * a.W * a.C;
-    if (a.vec) {
-      const int x0 = (a.W - 1) / 4 * 4;  // the last 4-pixel group a lane reads
-      dry_range(a.W % 4, 0, 1, "sig: 4-pixel loads need W a multiple of 4");
-      dry_access(a.frames, f, a.C == 3 ? 12 : 4, "sig: first pixels");
-      dry_access(a.frames, last_row + (a.C == 3 ? 3 * (int64_t)x0 : x0), a.C == 3 ? 12 : 4, "sig: last pixels");
-    } else {
-      dry_access(a.frames, f, a.C, "sig: first pixel");
-      dry_access(a.frames, last_row + (int64_t)(a.W - 1) * a.C, a.C, "sig: last pixel");
+  dry_lds(0, 4 * (int64_t)a.bpw * a.gw + 2 * (int64_t)a.W, (int64_t)lds, "sig: cells and column table");
+  dry_range((int64_t)a.parts * a.bpw, a.gh, (int64_t)a.gh + a.bpw, "sig: grid rows of the workgroups");
+  dry_range(((int64_t)(a.W - 1) * a.gw) / a.W, 0, a.gw, "sig: a column's cell");
+  const int64_t row_bytes = (int64_t)a.W * a.C;
+  int64_t px = 0;
+  for (int part = 0; part < a.parts; ++part) {
+    const int b0 = part * a.bpw, nb = a.gh - b0 < a.bpw ? a.gh - b0 : a.bpw;
+    if (nb <= 0) continue;
+    for (int e = 0; e < nb * a.sub * a.groups; ++e) {
+      const SigTask t = sig_task(a, e, b0);
+      dry_range(t.band, 0, nb, "sig: a task's grid row");
+      if (t.yb <= t.ya) continue;
+      dry_range(t.ya, 0, t.yb, "sig: a task's rows");
+      dry_range(t.yb, 1, (int64_t)a.H + 1, "sig: a task's rows past the frame");
+      dry_range(t.x0, 0, a.W, "sig: a task's columns past the row");
+      const int64_t cols = narrow ? a.W : 4;
+      dry_range(t.xb + cols, 1, (int64_t)a.W + 1, "sig: a task's loads past the row");
+      px += (int64_t)(t.yb - t.ya) * (narrow ? a.W : t.xb + 4 - t.x0);
+      // the frames' rows are alike: the first and the last frame
+      for (const int64_t b : {int64_t(0), n - 1}) {
+        const int64_t fb = b * a.frame_bytes + t.xb * a.C;
+        dry_access(a.frames, fb + t.ya * row_bytes, cols * a.C, "sig: a task's first row");
+        dry_access(a.frames, fb + (t.yb - 1) * row_bytes, cols * a.C, "sig: a task's last row");
+      }
     }
-    dry_access(a.out, 4 * b * a.nsig, 4 * (int64_t)a.nsig, "sig: signature row");
   }
+  dry_range(px - (int64_t)a.H * a.W, 0, 1, "sig: every pixel in one task");
+  dry_access(a.out, 0, 4 * n * a.nsig, "sig: signature rows");
 }
 
 // Address model of ngff_band_keep_kernel (dry run): each workgroup's
@@ -1221,6 +1313,12 @@ void model_band_keep(const BandKeepArgs& a, int64_t nwg, int64_t lds) {
   }
 }
 
+template <int C, bool NARROW, int UN>
+int launch_sig(const SigArgs& a, int64_t n, size_t lds, hipStream_t s) {
+  if (dry_run()) model_sig(a, n, NARROW, lds);
+  return launch("ngff_sig", ngff_sig_kernel<C, NARROW, UN>, dim3((unsigned)(n * a.parts)), dim3(kSigThreads), lds, s, a);
+}
+
 int run_signature(const uint8_t* frames, const NgffShape& sh, uint32_t* out, hipStream_t s) {
   SigArgs a;
   a.frames = frames;
@@ -1232,10 +1330,29 @@ int run_signature(const uint8_t* frames, const NgffShape& sh, uint32_t* out, hip
   a.gh = a.dhash ? 8 : sh.B;
   a.gw = a.dhash ? 9 : sh.B;
   a.nsig = (int32_t)sh.nbins;
-  a.vec = (reinterpret_cast<uintptr_t>(frames) % 4 == 0) && sh.W % 4 == 0 ? 1 : 0;
   a.out = out;
-  if (dry_run()) model_sig(a, sh.n);
-  return launch("ngff_sig", ngff_sig_kernel, dim3((unsigned)sh.n), dim3(kSigThreads), 0, s, a);
+  const bool narrow = sh.W < 4;
+  a.groups = narrow ? 1 : (sh.W + 3) / 4;
+  // row slices of at most 16 rows: enough tasks per frame for its workgroups
+  const int rows = (sh.H + a.gh - 1) / a.gh;
+  a.sub = (rows + 15) / 16;
+  a.slice = (rows + a.sub - 1) / a.sub;
+  a.lgh = __builtin_ctz((unsigned)a.gh);
+  // about 4 tasks per thread, but at least four workgroups per CU while the
+  // frames have the grid rows for it
+  const int64_t band_tasks = (int64_t)a.sub * a.groups;
+  int64_t parts = std::max<int64_t>(1, a.gh * band_tasks / (4 * kSigThreads));
+  parts = std::max(parts, (4 * (int64_t)device_cu_count() + sh.n - 1) / sh.n);
+  parts = std::min<int64_t>(parts, a.gh);
+  a.bpw = (int32_t)((a.gh + parts - 1) / parts);
+  a.parts = (a.gh + a.bpw - 1) / a.bpw;
+  const size_t lds = (size_t)a.bpw * a.gw * 4 + ((size_t)sh.W * 2 + 3) / 4 * 4;
+  if (sh.C == 3) {
+    if (narrow) return launch_sig<3, true, 1>(a, sh.n, lds, s);
+    return rows > 4 ? launch_sig<3, false, 8>(a, sh.n, lds, s) : launch_sig<3, false, 4>(a, sh.n, lds, s);
+  }
+  if (narrow) return launch_sig<1, true, 1>(a, sh.n, lds, s);
+  return launch_sig<1, false, 8>(a, sh.n, lds, s);
 }
 
 int run_histogram(const uint8_t* frames, const NgffShape& sh, uint32_t* hist, hipStream_t s,

@@ -52,9 +52,31 @@ def test_signal_rows_bit_exact(name, shape, G):
     assert np.array_equal(got, oracle.signature(f, okind, G))
 
 
+@pytest.mark.parametrize("name,shape,G", [("framediff", (2, 9, 2, 3), 2),       # rows of fewer than 4 pixels
+                                          ("framediff", (3, 5, 3, 1), 2),
+                                          ("framediff", (2, 16, 4, 3), 4),      # one column group
+                                          ("framediff", (2, 35, 5, 1), 4),      # a group that overlaps the one before
+                                          ("framediff", (2, 530, 67, 3), 32),   # 17 rows a grid row: two slices, 9 and 8
+                                          ("dhash", (1, 1031, 131, 3), 8),      # 9 slices a grid row, one frame
+                                          ("framediff", (1100, 12, 18, 3), 4),  # more frames than four per CU
+                                          ("dhash", (3, 8, 9, 3), 8)])          # one pixel per cell
+@pytest.mark.parametrize("offset", [0, 3])
+def test_signal_rows_task_edges(name, shape, G, offset):
+    """The signature kernel's tasks at their edges: short rows, the row's last
+    column group, row slices, workgroup splits, rows at any byte."""
+    kind, okind = KINDS[name]
+    rng = np.random.default_rng([2609, 3675, 66, shape[1], shape[2]])
+    f = rng.integers(0, 256, size=shape, dtype=np.uint8)
+    buf = torch.empty(f.nbytes + offset, dtype=torch.uint8, device="cuda")
+    view = buf[offset:].view(shape)
+    view.copy_(torch.from_numpy(f))
+    print(f"signal {name} shape={shape} G={G} offset={offset}", flush=True)
+    assert np.array_equal(gpu_rows(view, kind, G), oracle.signature(f, okind, G))
+
+
 @pytest.mark.parametrize("name", ["framediff", "dhash"])
 def test_signal_rows_unaligned_frames(name):
-    """Frames starting at an odd byte address take the byte-load path."""
+    """Frames starting at an odd byte address."""
     kind, okind = KINDS[name]
     rng = np.random.default_rng([2609, 3675, 65])
     f = rng.integers(0, 256, size=(3, 40, 48, 3), dtype=np.uint8)
