@@ -2,9 +2,9 @@
 //
 // cofie_mask_compact: the NGFF candidate set S_c as frame indices (Sec. 3.1 -
 //   3.2: the candidates are what the visual encoder runs on).  One workgroup
-//   walks the mask in chunks of 1024 x 16 frames: per-thread counts, a block
-//   exclusive scan, a running total across chunks.  One launch and no scratch
-//   for any n; the whole stream of even a C5-sized batch is a few chunks.
+//   walks the mask in chunks of up to 1024 x 16 frames: per-thread flag bits,
+//   a block exclusive scan, a running total across chunks.  One launch and no
+//   scratch for any n; even 16384 frames are one chunk.
 // cofie_gather_frames: frame refinement (Sec. 3.3): the rows of the frames in
 //   S_e, in the order given (chronological for a top-k), appended to a compact
 //   buffer -- the hidden states / cached keys and values / positions of the
@@ -12,6 +12,7 @@
 //   the output CSR; a copy kernel then streams every selected frame's
 //   contiguous byte range with 16-byte lanes (4-byte or byte lanes when the
 //   pointers or the row size are not aligned), bounded by the capacity.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -21,7 +22,6 @@ namespace cofie {
 namespace {
 
 constexpr int kGlueThreads = 1024;
-constexpr int kMaskPerThread = 16;
 
 // Exclusive prefix sum over the block (1024 threads); total in *total.
 __device__ int64_t block_exscan64(int64_t v, int64_t* total, int64_t* wsum) {
@@ -44,38 +44,79 @@ __device__ int64_t block_exscan64(int64_t v, int64_t* total, int64_t* wsum) {
   return before + x - v;
 }
 
-__global__ __launch_bounds__(kGlueThreads) void mask_compact_kernel(const uint8_t* mask, int64_t n,
-                                                                    int64_t seg_len, int64_t nseg,
-                                                                    int32_t* out_idx,
+// Exclusive prefix sum over the block (at most 1024 threads, total < 2^31).
+__device__ __forceinline__ int block_exscan32(int v, int* total, int* wsum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int i = 0; i < nw; ++i) {
+    if (i < wave) before += wsum[i];
+    all += wsum[i];
+  }
+  __syncthreads();
+  *total = all;
+  return before + x - v;
+}
+
+// PER consecutive frames per thread and chunk, as flag bits (one load where
+// PER frames are there and aligned).  Latency-bound: one workgroup, so what
+// counts is the chain load -> scan -> store; PER is the least of 1, 4 and 16
+// that takes the mask in one chunk.  (With 16 frames a thread at every size,
+// each read as a byte and tested for its stream's start by a 64-bit division,
+// 64 to 256 frames took 5.7 us, 16384 took 10.7: now 4.0 and 4.1.)
+template <int PER>
+__global__ __launch_bounds__(kGlueThreads) void mask_compact_kernel(const uint8_t* mask, uint32_t n, uint32_t seg_len,
+                                                                    int64_t nseg, int aligned, int32_t* out_idx,
                                                                     int32_t* out_seg_start) {
-  __shared__ int64_t wsum[16];
+  __shared__ int wsum[16];
   const int tid = threadIdx.x;
-  const int64_t per_chunk = (int64_t)kGlueThreads * kMaskPerThread;
-  int64_t base_count = 0;
-  for (int64_t c0 = 0; c0 < n; c0 += per_chunk) {
-    const int64_t f0 = c0 + (int64_t)tid * kMaskPerThread;
-    uint8_t m[kMaskPerThread];
-#pragma unroll
-    for (int j = 0; j < kMaskPerThread; ++j) m[j] = f0 + j < n ? mask[f0 + j] : 0;
-    int64_t cnt = 0;
-#pragma unroll
-    for (int j = 0; j < kMaskPerThread; ++j) cnt += m[j] != 0 ? 1 : 0;
-    int64_t total;
-    int64_t pos = base_count + block_exscan64(cnt, &total, wsum);
-#pragma unroll
-    for (int j = 0; j < kMaskPerThread; ++j) {
-      const int64_t f = f0 + j;
-      if (f < n) {
-        // this frame opens a stream segment: candidates before it
-        if (seg_len > 0 ? f % seg_len == 0 : f == 0) out_seg_start[seg_len > 0 ? f / seg_len : 0] = (int32_t)pos;
-        if (m[j] != 0) out_idx[pos++] = (int32_t)f;
+  int base_count = 0;
+  for (uint32_t c0 = 0; c0 < n; c0 += blockDim.x * PER) {
+    const uint32_t f0 = c0 + (uint32_t)tid * PER;
+    uint32_t bits = 0;  // bit j: frame f0 + j is a candidate
+    if (PER > 1 && aligned && f0 < n && n - f0 >= PER) {
+      uint32_t w[(PER + 3) / 4];
+      if constexpr (PER == 16) {
+        const uint4 v = *reinterpret_cast<const uint4*>(mask + f0);
+        w[0] = v.x;
+        w[1] = v.y;
+        w[2] = v.z;
+        w[3] = v.w;
+      } else {
+        w[0] = *reinterpret_cast<const uint32_t*>(mask + f0);
       }
+#pragma unroll
+      for (int j = 0; j < PER; ++j) bits |= ((w[j >> 2] >> (8 * (j & 3))) & 255u) ? 1u << j : 0u;
+    } else if (f0 < n) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const bool in = n - f0 > (uint32_t)j;
+        const uint8_t m = mask[in ? f0 + j : f0];
+        bits |= in && m ? 1u << j : 0u;
+      }
+    }
+    int total;
+    const int pos = base_count + block_exscan32(__builtin_popcount(bits), &total, wsum);
+    if (f0 < n) {
+      // streams that begin in these frames: the candidates before them
+      const uint32_t end = n - f0 < PER ? n : f0 + PER;
+      uint32_t s = (f0 + seg_len - 1) / seg_len;
+      for (uint32_t st = s * seg_len; st < end; st += seg_len, ++s)
+        out_seg_start[s] = pos + __builtin_popcount(bits & ((1u << (st - f0)) - 1u));
+      for (int at = pos; bits; bits &= bits - 1) out_idx[at++] = (int32_t)(f0 + __builtin_ctz(bits));
     }
     base_count += total;
   }
   if (tid == 0) {
     if (n == 0 && nseg > 0) out_seg_start[0] = 0;
-    out_seg_start[nseg] = (int32_t)base_count;
+    out_seg_start[nseg] = base_count;
   }
 }
 
@@ -259,8 +300,13 @@ int cofie_mask_compact(const uint8_t* mask, int64_t n, int64_t segment_len, int3
   if (!out_seg_start) return set_error(COFIE_EINVAL, "out_seg_start is NULL");
   if (n > 0 && (!mask || !out_idx)) return set_error(COFIE_EINVAL, "mask or out_idx is NULL");
   const int64_t nseg = segment_len > 0 ? ceil_div(n, segment_len) : 1;
-  return launch("glue_mask_compact", mask_compact_kernel, dim3(1), dim3(kGlueThreads), 0,
-                static_cast<hipStream_t>(stream), mask, n, segment_len, nseg, out_idx, out_seg_start);
+  const uint32_t seg = (uint32_t)(segment_len > 0 && segment_len < n ? segment_len : (n > 0 ? n : 1));
+  const int per = n <= kGlueThreads ? 1 : (n <= 4 * kGlueThreads ? 4 : 16);
+  const int64_t threads = std::min<int64_t>(kGlueThreads, std::max<int64_t>(64, (n + 64 * per - 1) / (64 * per) * 64));
+  const int aligned = reinterpret_cast<uintptr_t>(mask) % per == 0;
+  const auto kernel = per == 1 ? mask_compact_kernel<1> : (per == 4 ? mask_compact_kernel<4> : mask_compact_kernel<16>);
+  return launch("glue_mask_compact", kernel, dim3(1), dim3((unsigned)threads), 0, static_cast<hipStream_t>(stream), mask,
+                (uint32_t)n, seg, nseg, aligned, out_idx, out_seg_start);
 }
 
 int cofie_gather_frames(const void* src, int64_t n_rows, int64_t row_bytes, const int32_t* frame_offsets,
