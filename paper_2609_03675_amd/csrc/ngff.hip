@@ -852,6 +852,10 @@ struct BandKeepArgs {
   uint32_t* G;      // [n] keep-test words
 };
 
+// Frame of workgroup b of ngff_keep_wide_kernel (grid 8 c workgroups, dealt to
+// the XCDs in turn): XCD b % 8 takes the c consecutive frames from (b % 8) c.
+__host__ __device__ __forceinline__ int64_t keep_wide_frame(int64_t b, int64_t grid) { return (b & 7) * (grid >> 3) + (b >> 3); }
+
 __global__ __launch_bounds__(1024) void ngff_band_keep_kernel(BandKeepArgs a) {
   extern __shared__ __align__(16) uint32_t sm[];
   const RuleArgs& ru = a.rule;
@@ -932,6 +936,74 @@ __global__ __launch_bounds__(1024) void ngff_band_keep_kernel(BandKeepArgs a) {
       g |= (uint32_t)((Dadj > Dref ? Dadj : Dref) >= theta) << k;
     }
     a.G[t] = g;
+  }
+}
+
+// The same for wide rows (nbins a multiple of 256 NV; L_max <= 31): one
+// workgroup per frame, wave w taking the lags w + 1, w + 5, ..., lanes across
+// the bins.  No staging: a lane reads 16 bytes of a row at a time, four lags'
+// rows at once, straight from L2 (a workgroup that stages TB + L rows of 1024
+// bins in LDS fits TB = 5 frames and spends its time on the staging's load
+// round trips: 600 frames of 1024 bins 50 us, here 7 us; 16384 frames 1045 and 86).  Frames are dealt so
+// that each XCD takes consecutive ones: a row is read by the 31 workgroups
+// after it through one L2.
+template <int NV>
+__global__ __launch_bounds__(256) void ngff_keep_wide_kernel(BandKeepArgs a) {
+  __shared__ int32_t bl[32];  // D(t, t - k) at k - 1
+  const RuleArgs& ru = a.rule;
+  const int L = ru.L, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t t = keep_wide_frame(blockIdx.x, gridDim.x);
+  if (t >= a.n) return;
+  const int64_t seg = t / ru.seg_len, in_seg = t - seg * ru.seg_len;
+  const int kmax = in_seg < L ? (int)in_seg : L;  // t - k stays in the stream
+  const uint4* x = reinterpret_cast<const uint4*>(a.hist + t * a.nbins) + lane;
+  const int row_u4 = a.nbins / 4;
+  constexpr int K = 4;  // lags in flight per wave
+  for (int i0 = 0; wave + 1 + 4 * i0 <= L; i0 += K) {
+    uint32_t D[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) D[i] = 0;
+    if (wave + 1 + 4 * i0 <= kmax) {
+      for (int c = 0; c < row_u4; c += 64 * NV) {
+        uint4 u[NV], v[K][NV];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) u[j] = x[c + 64 * j];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          const int k = wave + 1 + 4 * (i0 + i);
+          const uint4* y = x - (int64_t)(k <= kmax ? k : 0) * row_u4;  // past the stream: D = 0
+#pragma unroll
+          for (int j = 0; j < NV; ++j) v[i][j] = y[c + 64 * j];
+        }
+        auto ad = [](uint32_t p, uint32_t q) __attribute__((always_inline)) { return p > q ? p - q : q - p; };
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+          for (int j = 0; j < NV; ++j)
+            D[i] += ad(u[j].x, v[i][j].x) + ad(u[j].y, v[i][j].y) + ad(u[j].z, v[i][j].z) + ad(u[j].w, v[i][j].w);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) D[i] += __shfl_xor(D[i], o);
+      const int k = wave + 1 + 4 * (i0 + i);
+      if (lane == 0 && k <= L) {
+        bl[k - 1] = (int32_t)D[i];
+        a.band[t * L + k - 1] = (int32_t)D[i];
+      }
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int64_t theta = theta_of(tau_of_segment(ru, seg), ru.twoM);
+    const int32_t Dadj = bl[0], Dref = bl[lane > 0 && lane <= L ? lane - 1 : 0];
+    const bool keep = lane > 0 && lane <= kmax && (Dadj > Dref ? Dadj : Dref) >= theta;
+    const uint64_t g = __ballot(keep);
+    if (lane == 0) {
+      a.adj[t] = Dadj;
+      a.G[t] = (uint32_t)g;
+    }
   }
 }
 
@@ -1330,6 +1402,28 @@ void model_band_keep(const BandKeepArgs& a, int64_t nwg, int64_t lds) {
   }
 }
 
+// Address model of ngff_keep_wide_kernel (dry run): every frame once, the rows
+// of its lags inside its stream, whole 16-byte loads, its outputs.
+void model_keep_wide(const BandKeepArgs& a, int64_t grid) {
+  const int L = a.rule.L;
+  dry_range(a.nbins % 256, 0, 1, "keep: bins of the wide rows");
+  dry_range(L, 1, 32, "keep: lags past the keep word");
+  int64_t frames = 0;
+  for (int64_t b = 0; b < grid; ++b) {
+    const int64_t t = keep_wide_frame(b, grid);
+    dry_range(t, 0, grid, "keep: a workgroup's frame");
+    if (t >= a.n) continue;
+    ++frames;
+    const int64_t in_seg = t % a.rule.seg_len, kmax = in_seg < L ? in_seg : L;
+    dry_access(a.hist, 4 * (t - kmax) * a.nbins, 4 * (kmax + 1) * a.nbins, "keep: histogram rows");
+    dry_access(a.band, 4 * t * L, 4 * (int64_t)L, "keep: band row");
+    dry_access(a.adj, 4 * t, 4, "keep: adjacent distance");
+    dry_access(a.G, 4 * t, 4, "keep: keep word");
+    if (a.rule.tau_seg) dry_access(a.rule.tau_seg, 4 * (t / a.rule.seg_len), 4, "keep: the stream's threshold");
+  }
+  dry_range(frames, a.n, a.n + 1, "keep: every frame once");
+}
+
 template <int C, bool NARROW, int UN>
 int launch_sig(const SigArgs& a, int64_t n, size_t lds, hipStream_t s) {
   if (dry_run()) model_sig(a, n, NARROW, lds);
@@ -1726,6 +1820,14 @@ __global__ void ngff_finish_kernel(uint8_t* mask_all, int64_t ld, int32_t S, int
   if (out_count) out_count[s] = (int32_t)kept;
 }
 
+// Rows of whole 1 KiB loads (a uint4 per lane) take the wide keep kernel: 256
+// bins, 600 frames: 16.6 us staged, 9.8 here; 512 bins, 300 frames: 13.3 and
+// 5.9; 4096 bins, 400 frames (band and next[] kernels of their own): 92 + 7
+// and 14.  Narrower rows leave lanes idle here and fit LDS well there.
+inline bool keep_wide(const NgffShape& sh, const uint32_t* hist) {
+  return sh.nbins % 256 == 0 && reinterpret_cast<uintptr_t>(hist) % 16 == 0;
+}
+
 // Workgroup sizes of the keep-rule kernels: small enough (4 waves, one per
 // SIMD) to run beside the QER score kernel's workgroups on the same CUs when
 // a caller overlaps the two on separate streams; the selection takes 1024
@@ -1757,7 +1859,7 @@ int filter_impl(const uint8_t* frames, const uint32_t* hist_in, const NgffShape&
   }
   const BandKeepPlan bp = plan_band_keep(sh, rp);
   const int chunk = select_chunk(rp.seg_len);
-  if (rp.gap_rule && bp.ok) {
+  if (rp.gap_rule && (bp.ok || (rp.L <= 31 && keep_wide(sh, hist)))) {
     BandKeepArgs bk;
     bk.hist = hist;
     bk.n = sh.n;
@@ -1768,11 +1870,19 @@ int filter_impl(const uint8_t* frames, const uint32_t* hist_in, const NgffShape&
     bk.band = w.band;
     bk.adj = w.adj;
     bk.G = w.G;
-    rc = allow_lds(ngff_band_keep_kernel, bp.lds);
-    if (rc) return rc;
-    if (dry_run()) model_band_keep(bk, ceil_div(sh.n, bp.TB), (int64_t)bp.lds);
-    rc = launch("ngff_keep", ngff_band_keep_kernel, dim3((unsigned)ceil_div(sh.n, bp.TB)), dim3(kKeepThreads),
-                bp.lds, s, bk);
+    if (keep_wide(sh, hist)) {
+      const int64_t grid = (sh.n + 7) / 8 * 8;
+      const auto kernel = sh.nbins % 1024 == 0 ? ngff_keep_wide_kernel<4>
+                                               : (sh.nbins % 512 == 0 ? ngff_keep_wide_kernel<2> : ngff_keep_wide_kernel<1>);
+      if (dry_run()) model_keep_wide(bk, grid);
+      rc = launch("ngff_keep", kernel, dim3((unsigned)grid), dim3(256), 0, s, bk);
+    } else {
+      rc = allow_lds(ngff_band_keep_kernel, bp.lds);
+      if (rc) return rc;
+      if (dry_run()) model_band_keep(bk, ceil_div(sh.n, bp.TB), (int64_t)bp.lds);
+      rc = launch("ngff_keep", ngff_band_keep_kernel, dim3((unsigned)ceil_div(sh.n, bp.TB)), dim3(kKeepThreads),
+                  bp.lds, s, bk);
+    }
     if (rc) return rc;
     const size_t lds = select_lds(chunk, true);
     rc = allow_lds(ngff_select_kernel<true>, lds);

@@ -37,6 +37,22 @@ def test_mask_compact(n, seg_len, p):
     assert np.array_equal(idx.cpu().numpy()[:seg[-1]], ref_idx)
 
 
+@pytest.mark.parametrize("n", [63, 64, 1023, 1024, 1025, 4095, 4096, 4097, 16400])
+@pytest.mark.parametrize("offset", [0, 1, 4])
+@pytest.mark.parametrize("seg_len", [0, 1, 5, 64])
+def test_mask_compact_chunk_edges(n, offset, seg_len):
+    """1, 4 and 16 frames per thread at their edges, masks at any byte."""
+    rng = np.random.default_rng([2609, 3675, 92, n, seg_len])
+    mask = (rng.random(n) < 0.4).astype(np.uint8) * 3
+    buf = torch.zeros(n + offset, dtype=torch.uint8, device="cuda")
+    buf[offset:].copy_(to_dev(mask))
+    idx, seg = B.cofie_mask_compact(buf[offset:], seg_len)
+    torch.cuda.synchronize()
+    ref_idx, ref_seg = oracle.mask_compact(mask, seg_len)
+    assert np.array_equal(seg.cpu().numpy(), ref_seg)
+    assert np.array_equal(idx.cpu().numpy()[:ref_seg[-1]], ref_idx)
+
+
 def test_compact_of_ngff_mask():
     """NGFF on the GPU, then the candidate list of every stream."""
     frames = synth.random_frames(11, 96, 24, 32, scenes=6)

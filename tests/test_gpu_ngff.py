@@ -73,6 +73,14 @@ def test_histogram_frames_at_any_byte(H, W, mode, bins, offset):
     assert np.array_equal(got, oracle.histogram(f if C == 3 else f[..., 0], bins, MODES[mode]))
 
 
+def test_histogram_split_frames_past_one_per_cu():
+    """A few more large frames than CUs with counters of 128 KiB: frames are
+    split between workgroups, whose counts meet in zeroed rows."""
+    f = synth.random_frames(5, 262, 479, 641)
+    got = gpu_hist(f, 8, "joint3d")
+    assert np.array_equal(got, oracle.histogram(f, 8, oracle.JOINT3D))
+
+
 def test_histogram_extreme_values():
     """All-0 and all-255 frames, and every byte value, land in the edge bins."""
     f = np.zeros((3, 16, 48, 3), dtype=np.uint8)
@@ -223,6 +231,23 @@ def test_filter_band_keep_geometry(n, seg_len, L_max, mode, bins):
     assert_filter_equal(run_filter(f, bins, mode, 0.25, L_max=L_max, M_min=4, seg_len=seg_len),
                         oracle_filter(f, bins, mode, np.float32(0.25), L_max=L_max, M_min=4,
                                       seg_len=seg_len))
+
+
+@pytest.mark.parametrize("n,seg_len,L_max,mode,bins", [
+    (1, 0, 30, "gray", 256),       # one frame: no lag inside the stream
+    (41, 0, 31, "gray", 256),      # 256 bins, the longest keep word, a grid past the frames
+    (67, 20, 1, "gray", 256),      # one lag, segments
+    (90, 33, 4, "joint3d", 8),     # 512 bins, one lag a wave
+    (64, 0, 17, "joint3d", 16),    # 4096 bins: several passes over a row
+    (50, 7, 30, "joint3d", 16)])   # streams shorter than L_max
+def test_filter_wide_rows(n, seg_len, L_max, mode, bins):
+    """Rows of whole 1 KiB loads take the keep kernel without LDS staging."""
+    f = synth.random_frames(n + L_max, n, 24, 40, scenes=9)
+    for tau in (0.05, 0.4):
+        s, m, h, k = run_filter(f, bins, mode, tau, L_max, 4, seg_len)
+        so, mo, ho, ko = oracle_filter(f, bins, mode, tau, L_max, 4, seg_len)
+        assert np.array_equal(h, ho) and np.array_equal(m, mo) and np.array_equal(k, ko)
+        assert np.array_equal(s.view(np.uint32), so.view(np.uint32))
 
 
 @pytest.mark.parametrize("seg_len,L_max", [(0, 30), (100, 9), (0, 45), (0, 0)])
