@@ -450,6 +450,9 @@ struct BandArgs {
   // window[stream][row] ([n / seg_len][wrows][nbins]) instead of hist
   const uint32_t* window;
   int32_t wrows;
+  // > 0: only the rows past the first wrows of every stream are computed, in
+  // `tiles` workgroups of TB rows per stream
+  int32_t tiles;
 };
 
 __device__ __forceinline__ const uint32_t* band_row(const BandArgs& a, int64_t r) {
@@ -463,9 +466,14 @@ __device__ __forceinline__ const uint32_t* band_row(const BandArgs& a, int64_t r
 __global__ __launch_bounds__(256) void ngff_band_kernel(BandArgs a) {
   extern __shared__ uint32_t rows[];
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * a.TB;
+  int64_t t0 = (int64_t)blockIdx.x * a.TB, end = a.n;
+  if (a.tiles) {
+    const int64_t sg = blockIdx.x / a.tiles;
+    t0 = sg * a.seg_len + a.wrows + (blockIdx.x - sg * a.tiles) * a.TB;
+    end = (sg + 1) * a.seg_len;
+  }
   const int64_t r0 = t0 - a.L > 0 ? t0 - a.L : 0;
-  const int64_t r1 = t0 + a.TB < a.n ? t0 + a.TB : a.n;
+  const int64_t r1 = t0 + a.TB < end ? t0 + a.TB : end;
   if (a.stride) {
     // all loads of a batch are issued before their stores (clamped indices)
     const int64_t total = (r1 - r0) * a.nbins;
@@ -1594,8 +1602,10 @@ int run_band(const uint32_t* hist, const NgffShape& sh, const RulePlan& rp, int3
   const size_t row = (size_t)(sh.nbins + 1) * 4;
   // about one workgroup per CU (a 94-row push band took 45 us with 64 frames
   // per workgroup, i.e. two workgroups), at most 64 frames each
+  // (with a window only the rows past it, per stream)
   const int64_t cus = device_cu_count();
-  int TB = (int)std::min<int64_t>(64, std::max<int64_t>(1, (sh.n + cus - 1) / cus));
+  const int64_t todo = window ? rp.nseg * (rp.seg_len - wrows) : sh.n;
+  int TB = (int)std::min<int64_t>(64, std::max<int64_t>(1, (todo + cus - 1) / cus));
   while (TB > 1 && (size_t)(TB + rp.L) * row > budget) TB >>= 1;
   size_t lds = (size_t)(TB + rp.L) * row;
   b.TB = TB;
@@ -1605,9 +1615,11 @@ int run_band(const uint32_t* hist, const NgffShape& sh, const RulePlan& rp, int3
     lds = 0;
   }
   b.band = band;
+  b.tiles = window ? ceil_div(rp.seg_len - wrows, TB) : 0;
+  const int64_t wgs = window ? rp.nseg * b.tiles : ceil_div(sh.n, TB);
   int rc = allow_lds(ngff_band_kernel, lds);
   if (rc) return rc;
-  return launch("ngff_band", ngff_band_kernel, dim3((unsigned)ceil_div(sh.n, TB)), dim3(256), lds, s, b);
+  return launch("ngff_band", ngff_band_kernel, dim3((unsigned)wgs), dim3(256), lds, s, b);
 }
 
 RuleArgs rule_args(const NgffShape& sh, const RulePlan& rp, const cofie_keep_rule* r,
@@ -1636,14 +1648,14 @@ int validate_rule(const cofie_keep_rule* r) {
 // The keep rule decided frame by frame as a stream grows (Sec. 3.1: the model
 // sees the current video prefix).  A push histograms the new frames of every
 // stream into a per-stream buffer [L window rows | nb new rows] (the window =
-// the L = L_max frames before the push, carried in the state), computes the
-// band of that buffer, and one workgroup per stream decides the new frames:
+// the L = L_max frames before the push, carried in the state), and one workgroup
+// per stream computes the new frames' band rows and decides the new frames:
 // next[r] for the carried last kept frame and every new frame (open at the
 // batch end: no keep found within the frames seen -> "beyond"), the chain
 // walked from the carried frame, r(t) by a block prefix maximum, the scores.
 // The end-of-stream safeguards (last frame, M_min top-up) wait for finish.
 struct PushArgs {
-  const int32_t* band;   // [S][L + nb][L]
+  const int32_t* band;   // [S][L + nb][L] (rows L.. of each stream); null: computed here
   int32_t L;             // L_max (>= 1): band width and gap rule
   int32_t nb;            // new frames per stream in this push (<= 1024)
   int64_t t0;            // frames of each stream before this push
@@ -1661,22 +1673,80 @@ struct PushArgs {
   int64_t nbins;
 };
 
+// LDS words of ngff_push_kernel: the new frames' band rows and three words per
+// frame, then (FUSED) the histograms of the window and the new frames.
+__host__ __device__ constexpr int64_t push_words(int64_t nb, int64_t L) { return nb * L + 3 * nb + 1; }
+
+// LDS stride of a histogram row: odd, so that lanes reading one bin of
+// consecutive rows hit distinct banks.
+__host__ __device__ constexpr int push_stride(int64_t nbins) { return (int)nbins | 1; }
+
+// FUSED: the band rows of the new frames are computed here, from the window's
+// and the new frames' histograms staged in LDS (lanes split the (frame, lag)
+// pairs and the bins), and the window is rewritten from LDS; otherwise they
+// come from ngff_band_kernel.  A push of few frames is bound by its launches
+// and their load latency, not by these sums: 32 streams of
+// 1 frame, 96 bins, 22.7 us with a band kernel over all L + 1 rows between, 20.7
+// with one over the new rows, 13.9 here.
+template <bool FUSED>
 __global__ __launch_bounds__(1024) void ngff_push_kernel(PushArgs a) {
   extern __shared__ int32_t psm[];
   int32_t* bandL = psm;                          // [nb][L]
   int32_t* next_sh = bandL + a.nb * a.L;         // [nb + 1]: slot 0 = carried frame, 1 + j = new frame j
   int32_t* keep_sh = next_sh + a.nb + 1;         // [nb]
   int32_t* incl_sh = keep_sh + a.nb;             // [nb]
+  uint32_t* rows = reinterpret_cast<uint32_t*>(psm + push_words(a.nb, a.L));  // FUSED: [L + nb][RS]
+  const int RS = push_stride(a.nbins);
   __shared__ int64_t theta_sh;
   __shared__ int wtmp[16];
   const int s = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int L = a.L, nb = a.nb;
   const int64_t t0 = a.t0, tend = t0 + nb;
-  const int32_t* src = a.band + ((int64_t)s * (L + nb) + L) * L;
-  for (int i = tid; i < nb * L; i += nthr) bandL[i] = src[i];
-  for (int j = tid; j < nb; j += nthr) keep_sh[j] = 0;
-  if (tid == 0) theta_sh = theta_of(a.tau_seg ? a.tau_seg[s] : a.tau, a.twoM);
   const int64_t rc = t0 > 0 ? a.r_state[s] : -1;  // carried last kept frame
+  uint32_t* win = a.window + (int64_t)s * L * a.nbins;
+  uint32_t* cs = a.comb + (int64_t)s * (L + nb) * a.nbins;
+  for (int j = tid; j < nb; j += nthr) keep_sh[j] = 0;
+  if constexpr (FUSED) {
+    const int nbins = (int)a.nbins;
+    const int lane = tid & 63, nwave = nthr >> 6;
+    for (int r0 = tid >> 6; r0 < L + nb; r0 += 4 * nwave) {  // a row per wave, four in flight
+      for (int b = lane; b < nbins; b += 64) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int r = r0 + u * nwave < L + nb ? r0 + u * nwave : r0;
+          v[u] = (r < L ? win : cs)[r * nbins + b];  // comb's first L rows are unused: the window holds them
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (r0 + u * nwave < L + nb) rows[(r0 + u * nwave) * RS + b] = v[u];
+      }
+    }
+    if (tid == nthr - 1) theta_sh = theta_of(a.tau_seg ? a.tau_seg[s] : a.tau, a.twoM);
+    __syncthreads();
+    const int npairs = nb * L;
+    int LPP = 1;  // lanes per pair, a power of two <= 64: a group never straddles a wave
+    while (LPP < 64 && 2 * LPP * npairs <= nthr) LPP <<= 1;
+    const int sub = tid & (LPP - 1), groups = nthr / LPP;
+    for (int p0 = 0; p0 < npairs; p0 += groups) {  // whole passes: every lane runs the shuffles
+      const int pi = p0 + tid / LPP;
+      const bool ok = pi < npairs;
+      const int j = ok ? pi / L : 0, k = ok ? pi - j * L + 1 : 1;
+      const uint32_t* x = rows + (L + j) * RS;
+      const uint32_t* y = x - k * RS;
+      uint32_t D = 0;
+      for (int b = sub; b < nbins; b += LPP) {
+        const uint32_t u = x[b], v = y[b];
+        D += u > v ? u - v : v - u;
+      }
+      for (int o = 1; o < LPP; o <<= 1) D += __shfl_xor(D, o, LPP);
+      if (ok && sub == 0) bandL[pi] = (int32_t)D;
+    }
+  } else {
+    const int32_t* src = a.band + ((int64_t)s * (L + nb) + L) * L;
+    for (int i = tid; i < nb * L; i += nthr) bandL[i] = src[i];
+    if (tid == 0) theta_sh = theta_of(a.tau_seg ? a.tau_seg[s] : a.tau, a.twoM);
+  }
   __syncthreads();
   const int64_t theta = theta_sh;
   // next[r]: the first u in (r, r + L] (u >= t0) whose max(D(u, u-1), D(u, r))
@@ -1749,9 +1819,14 @@ __global__ __launch_bounds__(1024) void ngff_push_kernel(PushArgs a) {
   // new frames).  When nb < L this shifts the window down in place, so it is
   // copied in chunks, each read completely before any of it is written (later
   // chunks only read above what earlier chunks wrote).
-  uint32_t* win = a.window + (int64_t)s * L * a.nbins;
-  uint32_t* cs = a.comb + (int64_t)s * (L + nb) * a.nbins;
   const int64_t total = (int64_t)L * a.nbins;
+  if constexpr (FUSED) {
+    const int nbins = (int)a.nbins;
+    for (int r = tid >> 6; r < L; r += nthr >> 6)
+      for (int b = tid & 63; b < nbins; b += 64) win[r * nbins + b] = rows[(nb + r) * RS + b];
+    for (int64_t i = tid; i < (int64_t)nb * a.nbins; i += nthr) cs[total + i] = 0u;
+    return;
+  }
   constexpr int V = 4;
   for (int64_t c0 = 0; c0 < total; c0 += (int64_t)V * nthr) {
     uint32_t v[V];
@@ -1773,8 +1848,6 @@ __global__ __launch_bounds__(1024) void ngff_push_kernel(PushArgs a) {
   // them when several workgroups share a frame), so that push needs no fill
   for (int64_t i = tid; i < (int64_t)nb * a.nbins; i += nthr) cs[(int64_t)L * a.nbins + i] = 0u;
 }
-
-// comb[s][0..L) <- window[s] (dir 0) or window[s] <- comb[s][nb..nb+L) (dir 1)
 
 // End of the streams: frame T-1 kept, then the M_min top-up (one thread per
 // stream); out_added row s receives the frames this adds, increasing and -1
@@ -1827,6 +1900,12 @@ __global__ void ngff_finish_kernel(uint8_t* mask_all, int64_t ld, int32_t S, int
 inline bool keep_wide(const NgffShape& sh, const uint32_t* hist) {
   return sh.nbins % 256 == 0 && reinterpret_cast<uintptr_t>(hist) % 16 == 0;
 }
+
+// |difference| terms of a stream's new band rows up to which its one workgroup
+// computes them (above, a kernel of many workgroups per stream does).  Per
+// push, 32 streams of 16 frames (46 thousand terms): 61.5 us in one kernel,
+// 67.5 in two; 8 streams of 45 (130 thousand): 65.2 and 64.1.
+constexpr int64_t kPushTerms = 49152;
 
 // Workgroup sizes of the keep-rule kernels: small enough (4 waves, one per
 // SIMD) to run beside the QER score kernel's workgroups on the same CUs when
@@ -2284,18 +2363,24 @@ int cofie_ngff_stream_push(cofie_ngff_stream* st, const uint8_t* frames, int64_t
     st->zero_nb = -1;                // until this push's kernel has zeroed them again
     int rc = run_histogram(frames, sh, comb, s, map);
     if (rc) return rc;
-    // the band reads each stream's first L rows (the frames before t0) from the window
-    NgffShape bsh = st->sh;
-    bsh.n = rows;
-    RulePlan rp;
-    rp.seg_len = L + nb;
-    rp.nseg = S;
-    rp.gap_rule = true;
-    rp.L = L;
-    rc = run_band(comb, bsh, rp, band, s, st->window, L);
-    if (rc) return rc;
+    // one workgroup per stream computes the band rows too while it has at most
+    // kPushTerms |difference| terms and the histograms fit its LDS
+    const size_t words = (size_t)push_words(nb, L), hist_words = (size_t)(L + nb) * push_stride(st->sh.nbins);
+    const bool fused = (int64_t)nb * L * st->sh.nbins <= kPushTerms && (words + hist_words) * 4 <= kLdsBudget;
+    if (!fused) {
+      // the band reads each stream's first L rows (the frames before t0) from the window
+      NgffShape bsh = st->sh;
+      bsh.n = rows;
+      RulePlan rp;
+      rp.seg_len = L + nb;
+      rp.nseg = S;
+      rp.gap_rule = true;
+      rp.L = L;
+      rc = run_band(comb, bsh, rp, band, s, st->window, L);
+      if (rc) return rc;
+    }
     PushArgs pa;
-    pa.band = band;
+    pa.band = fused ? nullptr : band;
     pa.L = L;
     pa.nb = nb;
     pa.t0 = st->t0;
@@ -2310,10 +2395,11 @@ int cofie_ngff_stream_push(cofie_ngff_stream* st, const uint8_t* frames, int64_t
     pa.comb = comb;
     pa.window = st->window;
     pa.nbins = st->sh.nbins;
-    const size_t lds = ((size_t)nb * L + 3 * (size_t)nb + 1) * sizeof(int32_t);
-    rc = allow_lds(ngff_push_kernel, lds);
+    const size_t lds = (words + (fused ? hist_words : 0)) * 4;
+    const auto kernel = fused ? ngff_push_kernel<true> : ngff_push_kernel<false>;
+    rc = allow_lds(kernel, lds);
     if (rc) return rc;
-    rc = launch("ngff_push", ngff_push_kernel, dim3(S), dim3(1024), lds, s, pa);
+    rc = launch("ngff_push", kernel, dim3(S), dim3(1024), lds, s, pa);
     if (rc) return rc;
     st->zero_nb = nb;
     st->t0 += nb;

@@ -92,6 +92,17 @@ def test_push_modes_and_streams(mode, bins):
                tau_per_stream=np.array([0.02, 0.08, 0.3], np.float32))
 
 
+@pytest.mark.parametrize("mode,bins,L_max,batches", [
+    ("per_channel", 32, 30, [17, 18, 1, 17, 27]),  # one kernel per push up to 17 frames, the band kernel from 18
+    ("gray", 2, 1, [1, 1, 40, 2, 36]),             # the shortest window, two bins, a push longer than it
+    ("joint3d", 16, 3, [2, 5, 1, 40]),             # 4096 bins: 9 rows of histograms fit LDS, 40 do not
+    ("gray", 64, 31, [31, 30, 1, 18])])            # an even row length; pushes of a window and one less
+def test_push_one_kernel_or_two(mode, bins, L_max, batches):
+    T = sum(batches)
+    frames = np.stack([synth.random_frames(60 + s, T, 12, 20, scenes=9) for s in range(2)])
+    run_stream(frames, bins, mode, 0.1, L_max, 4, batches)
+
+
 def test_push_matches_one_shot_filter_on_workload():
     """Eight streams of the multi-stream workload pushed 64 frames at a time:
     after finish, the masks and scores equal one cofie_ngff_filter call over
