@@ -89,6 +89,16 @@ def test_qer_shapes(dtype, n_q, H_q, H_kv, d):
         clean(dr, "shapes")
 
 
+@pytest.mark.parametrize("n_q,H_q,H_kv,d,n_vis", [
+    (32, 8, 8, 128, 500), (33, 8, 8, 128, 8191), (64, 8, 8, 128, 8193), (65, 8, 8, 128, 16385), (128, 4, 4, 64, 32785),
+    (20, 2, 2, 64, 70001), (129, 2, 2, 64, 4500), (48, 28, 4, 128, 20000), (50, 8, 2, 64, 70000), (70, 4, 1, 128, 300)])
+def test_streaming_score_kernel(n_q, H_q, H_kv, d, n_vis):
+    """The streaming score kernel's plans: slices, chunks, slots, rounds."""
+    with B.DryRun() as dr:
+        qer_single(dr, n_q, H_q, H_kv, d, [n_vis - 5, 5], "bf16", 2)
+        clean(dr, "streaming score kernel")
+
+
 # SOFTMAX with grouped bf16 heads of d = 128 (one query) takes the grouped-head
 # kernel: every instance, ragged rows and tiles, fewer tiles than key ranges
 SOFT_GRP = [(48, 28, 4, [222] * 8 + [224]),   # the high-res heads

@@ -68,6 +68,29 @@ def test_shapes(dtype, n_q, H_q, H_kv, d):
         run_case(Q, K, offs, H_q, H_kv, d, k, dtype=dtype)
 
 
+# (n_q, H_q, H_kv, d, keys) at the edges of the streaming score kernel's plan:
+# contraction slices by tiles per CU, query chunks, key slots, rounds
+STRM_EDGES = [(32, 8, 8, 128, 500),       # eight slices, fewer tiles than CUs
+              (33, 8, 8, 128, 8191),      # two tiles per CU, a ragged last one; rows past one chunk of eight slices
+              (64, 8, 8, 128, 8193),      # four slices, four row blocks
+              (65, 8, 8, 128, 16385),     # two slices, eight row blocks
+              (128, 4, 4, 64, 32785),     # one slice, four segments for four slots
+              (20, 2, 2, 64, 70001),      # two segments, two rounds per workgroup
+              (129, 2, 2, 64, 4500),      # a second chunk of one row
+              (48, 28, 4, 128, 20000),    # three query terms, two slices
+              (50, 8, 2, 64, 70000),      # three terms, one slice, two segments, two rounds
+              (70, 4, 1, 128, 300),       # three terms, two chunks
+              (17, 16, 1, 64, 300)]       # one segment: the general score kernel
+
+
+@pytest.mark.parametrize("n_q,H_q,H_kv,d,n_vis", STRM_EDGES)
+def test_streaming_score_kernel_edges(n_q, H_q, H_kv, d, n_vis):
+    """fp32 sums of exact products: within BF16_REGRESSION of the oracle."""
+    offs = synth.frame_offsets([n_vis // 7] * 6 + [n_vis - 6 * (n_vis // 7)])
+    Q, K = synth.random_qk(n_q + n_vis, n_q, n_vis, H_q, H_kv, d, "bf16")
+    run_case(Q, K, offs, H_q, H_kv, d, 3, dtype="bf16", regression=True)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_q,H_q,H_kv,d", [(8, 4, 4, 32), (40, 4, 2, 16), (70, 2, 2, 32)])
 def test_softmax_mode(dtype, n_q, H_q, H_kv, d):
