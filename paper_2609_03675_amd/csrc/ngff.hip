@@ -27,6 +27,7 @@
 // quotient and an exact midpoint test beyond), so they are bit-identical to
 // any correct implementation.
 #include <cstring>
+#include <type_traits>
 #include <vector>
 #include "common.h"
 
@@ -274,13 +275,13 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, int64_t count) {
 // reads a byte twice).  A lane keeps its 4 columns' sums in registers over the
 // task's rows and adds them to the cells once, at the task's end: per 12 bytes
 // about 30 VALU operations (two 4-byte dot products, a shift-add and one
-// 24-bit multiply a luma) and 1/16 of the LDS additions of one per row.  Rows
-// start at any byte: the loads are byte-aligned dwords.  600 frames of
+// 24-bit multiply a luma) and 1/16 of the LDS additions of one per row.  600 frames of
 // 480 x 853, frame difference, whole filter call: 1001 us with one workgroup
 // of 4 waves per frame, byte loads and an LDS addition a pixel; 228 us here.
 struct SigArgs {
   const uint8_t* frames;
   int64_t frame_bytes;
+  int64_t total;   // bytes of all frames
   int32_t H, W, C;
   int32_t gh, gw;  // gh a power of two
   int32_t lgh;     // log2 gh
@@ -335,13 +336,21 @@ __device__ __forceinline__ uint32_t luma_dot(uint32_t px) {
 
 typedef uint32_t u32_any __attribute__((aligned(1)));  // a dword at any byte
 
-// The 4 pixels at p as raw words: 12 bytes of RGB or 4 of gray.
-template <int C>
-struct SigPx {
-  uint32_t w[C];
-};
+// How the 4 pixels of a task's row (12 bytes of RGB or 4 of gray) are read.
+// kSigAligned: every row starts at a multiple of 4.  kSigAny: the aligned
+// words around them, then a byte shift, but for the tasks whose words would
+// reach outside the frames, which use byte-aligned loads (those alone for
+// every task took 163 us where aligned rows take 136: 600 frames of 480 x 853
+// against 852).  kSigNarrow: rows of fewer than 4 pixels, byte by byte.
+enum SigLoad { kSigAligned = 0, kSigAny = 1, kSigNarrow = 2 };
 
-template <int C, bool NARROW, int UN>
+// Words a kSigAny task may touch: from its first pixel's word to the word
+// after its last pixel.
+__host__ __device__ __forceinline__ bool sig_edge(int64_t first, int64_t last_end, int64_t total) {
+  return first < 3 || last_end + 4 > total;
+}
+
+template <int C, int LOAD, int UN>
 __global__ __launch_bounds__(kSigThreads) void ngff_sig_kernel(SigArgs a) {
   extern __shared__ uint32_t cell[];  // [bpw][gw], then the column table [W] (uint16)
   uint16_t* gcol = reinterpret_cast<uint16_t*>(cell + a.bpw * a.gw);
@@ -361,38 +370,62 @@ __global__ __launch_bounds__(kSigThreads) void ngff_sig_kernel(SigArgs a) {
     const uint8_t* p = f + (int64_t)t.ya * row_bytes + t.xb * C;
     const int rows = t.yb - t.ya;
     uint32_t s[4] = {0u, 0u, 0u, 0u};
-    if constexpr (NARROW) {
+    if constexpr (LOAD == kSigNarrow) {
       for (int y = 0; y < rows; ++y)
         for (int i = 0; i < a.W; ++i) {
           const uint8_t* px = p + y * row_bytes + i * C;
           s[i & 3] += C == 3 ? luma_bt601(px[0], px[1], px[2]) : px[0];
         }
     } else {
-      for (int y0 = 0; y0 < rows; y0 += UN) {
-        SigPx<C> v[UN];
+      // the lumas of a row's 4 pixels, added to the column sums
+      auto add = [&](const uint32_t (&w)[C], bool in) __attribute__((always_inline)) {
+        uint32_t px[4];
+        if constexpr (C == 3) {
+          px[0] = luma_dot(w[0]);
+          px[1] = luma_dot(__builtin_amdgcn_alignbyte(w[1], w[0], 3));
+          px[2] = luma_dot(__builtin_amdgcn_alignbyte(w[2], w[1], 2));
+          px[3] = luma_dot(w[2] >> 8);
+        } else {
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {  // rows past the task's repeat its last and are not added
-          const int y = y0 + u < rows ? y0 + u : rows - 1;
-          const u32_any* q = reinterpret_cast<const u32_any*>(p + y * row_bytes);
-#pragma unroll
-          for (int i = 0; i < C; ++i) v[u].w[i] = __builtin_nontemporal_load(q + i);
+          for (int i = 0; i < 4; ++i) px[i] = (w[0] >> (8 * i)) & 255u;
         }
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-          uint32_t l[4];
-          if constexpr (C == 3) {
-            const uint32_t w0 = v[u].w[0], w1 = v[u].w[1], w2 = v[u].w[2];
-            l[0] = luma_dot(w0);
-            l[1] = luma_dot(__builtin_amdgcn_alignbyte(w1, w0, 3));
-            l[2] = luma_dot(__builtin_amdgcn_alignbyte(w2, w1, 2));
-            l[3] = luma_dot(w2 >> 8);
-          } else {
+        for (int i = 0; i < 4; ++i) s[i] += in ? px[i] : 0u;
+      };
+      const int64_t first = p - a.frames, last_end = first + (rows - 1) * row_bytes + 4 * C;
+      if (LOAD == kSigAligned || sig_edge(first, last_end, a.total)) {
+        for (int y0 = 0; y0 < rows; y0 += UN) {
+          uint32_t v[UN][C];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) l[i] = (v[u].w[0] >> (8 * i)) & 255u;
+          for (int u = 0; u < UN; ++u) {  // rows past the task's repeat its last and are not added
+            const int y = y0 + u < rows ? y0 + u : rows - 1;
+            using Word = typename std::conditional<LOAD == kSigAligned, const uint32_t, const u32_any>::type;
+            Word* q = reinterpret_cast<Word*>(p + y * row_bytes);
+#pragma unroll
+            for (int i = 0; i < C; ++i) v[u][i] = __builtin_nontemporal_load(q + i);
           }
-          const bool in = y0 + u < rows;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) s[i] += in ? l[i] : 0u;
+          for (int u = 0; u < UN; ++u) add(v[u], y0 + u < rows);
+        }
+      } else {
+        for (int y0 = 0; y0 < rows; y0 += UN) {
+          uint32_t v[UN][C + 1], sh[UN];
+#pragma unroll
+          for (int u = 0; u < UN; ++u) {
+            const int y = y0 + u < rows ? y0 + u : rows - 1;
+            const uint8_t* at = p + y * row_bytes;
+            sh[u] = (uint32_t)reinterpret_cast<uintptr_t>(at) & 3u;
+            const uint32_t* q = reinterpret_cast<const uint32_t*>(at - sh[u]);
+#pragma unroll
+            for (int i = 0; i <= C; ++i) v[u][i] = __builtin_nontemporal_load(q + i);
+          }
+#pragma unroll
+          for (int u = 0; u < UN; ++u) {
+            uint32_t w[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) w[i] = __builtin_amdgcn_alignbyte(v[u][i + 1], v[u][i], sh[u]);
+            add(w, y0 + u < rows);
+          }
         }
       }
     }
@@ -1352,7 +1385,12 @@ struct HistMap {  // see HistArgs: group = 0 is the identity
 // Address model of ngff_sig_kernel (dry run): every task's rows as its loads
 // read them, the LDS column table and cell counters, the output rows.  Every
 // pixel belongs to exactly one task's columns.
-void model_sig(const SigArgs& a, int64_t n, bool narrow, size_t lds) {
+void model_sig(const SigArgs& a, int64_t n, int load, size_t lds) {
+  const bool narrow = load == kSigNarrow;
+  dry_range(a.total - n * a.frame_bytes, 0, 1, "sig: bytes of the frames");
+  const uintptr_t base = reinterpret_cast<uintptr_t>(a.frames);
+  if (load == kSigAligned)
+    dry_range((int64_t)((base | (uintptr_t)a.frame_bytes | (uintptr_t)(a.W * a.C)) & 3), 0, 1, "sig: rows at words");
   dry_range(a.W, 1, kSigMaxW + 1, "sig: columns past the column table");
   dry_range((int64_t)a.H * a.W * a.C, 1, a.frame_bytes + 1, "sig: pixels past the frame");
   dry_lds(0, 4 * (int64_t)a.bpw * a.gw + 2 * (int64_t)a.W, (int64_t)lds, "sig: cells and column table");
@@ -1376,8 +1414,14 @@ void model_sig(const SigArgs& a, int64_t n, bool narrow, size_t lds) {
       // the frames' rows are alike: the first and the last frame
       for (const int64_t b : {int64_t(0), n - 1}) {
         const int64_t fb = b * a.frame_bytes + t.xb * a.C;
-        dry_access(a.frames, fb + t.ya * row_bytes, cols * a.C, "sig: a task's first row");
-        dry_access(a.frames, fb + (t.yb - 1) * row_bytes, cols * a.C, "sig: a task's last row");
+        const int64_t first = fb + t.ya * row_bytes, last = fb + (t.yb - 1) * row_bytes;
+        if (load == kSigAny && !sig_edge(first, last + 4 * a.C, a.total)) {
+          for (int64_t at : {first, last})
+            dry_access(a.frames, at - (int64_t)((base + (uintptr_t)at) & 3), 4 * (a.C + 1), "sig: a task's words");
+        } else {
+          dry_access(a.frames, first, cols * a.C, "sig: a task's first row");
+          dry_access(a.frames, last, cols * a.C, "sig: a task's last row");
+        }
       }
     }
   }
@@ -1432,10 +1476,20 @@ void model_keep_wide(const BandKeepArgs& a, int64_t grid) {
   dry_range(frames, a.n, a.n + 1, "keep: every frame once");
 }
 
-template <int C, bool NARROW, int UN>
+template <int C, int LOAD, int UN>
 int launch_sig(const SigArgs& a, int64_t n, size_t lds, hipStream_t s) {
-  if (dry_run()) model_sig(a, n, NARROW, lds);
-  return launch("ngff_sig", ngff_sig_kernel<C, NARROW, UN>, dim3((unsigned)(n * a.parts)), dim3(kSigThreads), lds, s, a);
+  if (dry_run()) model_sig(a, n, LOAD, lds);
+  return launch("ngff_sig", ngff_sig_kernel<C, LOAD, UN>, dim3((unsigned)(n * a.parts)), dim3(kSigThreads), lds, s, a);
+}
+
+template <int C>
+int launch_sig_c(const SigArgs& a, int64_t n, size_t lds, hipStream_t s) {
+  if (a.W < 4) return launch_sig<C, kSigNarrow, 1>(a, n, lds, s);
+  const uintptr_t bits = reinterpret_cast<uintptr_t>(a.frames) | (uintptr_t)a.frame_bytes | (uintptr_t)(a.W * C);
+  // rows in flight: all of a full task's 16 where they stay in registers
+  // (1080p 253 -> 250 us), 4 for grids that leave few rows a task
+  if (bits % 4 == 0) return a.slice > 4 ? launch_sig<C, kSigAligned, 16>(a, n, lds, s) : launch_sig<C, kSigAligned, 4>(a, n, lds, s);
+  return a.slice > 4 ? launch_sig<C, kSigAny, 8>(a, n, lds, s) : launch_sig<C, kSigAny, 4>(a, n, lds, s);
 }
 
 int run_signature(const uint8_t* frames, const NgffShape& sh, uint32_t* out, hipStream_t s) {
@@ -1450,8 +1504,8 @@ int run_signature(const uint8_t* frames, const NgffShape& sh, uint32_t* out, hip
   a.gw = a.dhash ? 9 : sh.B;
   a.nsig = (int32_t)sh.nbins;
   a.out = out;
-  const bool narrow = sh.W < 4;
-  a.groups = narrow ? 1 : (sh.W + 3) / 4;
+  a.total = sh.n * sh.frame_bytes;
+  a.groups = (sh.W + 3) / 4;
   // row slices of at most 16 rows: enough tasks per frame for its workgroups
   const int rows = (sh.H + a.gh - 1) / a.gh;
   a.sub = (rows + 15) / 16;
@@ -1466,12 +1520,7 @@ int run_signature(const uint8_t* frames, const NgffShape& sh, uint32_t* out, hip
   a.bpw = (int32_t)((a.gh + parts - 1) / parts);
   a.parts = (a.gh + a.bpw - 1) / a.bpw;
   const size_t lds = (size_t)a.bpw * a.gw * 4 + ((size_t)sh.W * 2 + 3) / 4 * 4;
-  if (sh.C == 3) {
-    if (narrow) return launch_sig<3, true, 1>(a, sh.n, lds, s);
-    return rows > 4 ? launch_sig<3, false, 8>(a, sh.n, lds, s) : launch_sig<3, false, 4>(a, sh.n, lds, s);
-  }
-  if (narrow) return launch_sig<1, true, 1>(a, sh.n, lds, s);
-  return launch_sig<1, false, 8>(a, sh.n, lds, s);
+  return sh.C == 3 ? launch_sig_c<3>(a, sh.n, lds, s) : launch_sig_c<1>(a, sh.n, lds, s);
 }
 
 int run_histogram(const uint8_t* frames, const NgffShape& sh, uint32_t* hist, hipStream_t s,
