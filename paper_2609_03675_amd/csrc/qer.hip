@@ -10,18 +10,16 @@
 // as three bf16 terms hi + mid + lo whose sum is exactly it, so the bf16 MFMA
 // multiplies exact representations of the fp32 sum.
 //
-// qer_strm (qer_strm.hip): LOGIT scores of bf16 rows of whole 128-byte
-//   segments, at least two -- every model's heads.
-// qer_score: fp32 rows, other bf16 rows and the SOFTMAX passes.  One 8-wave
-//   workgroup per CU; each wave owns MB x 16 visual tokens
-//   and all (<= 64, or 128 in eight blocks) query rows of one chunk, over the
-//   whole contraction, or over one of NS slices of it where tiles are too few
-//   to give every wave of the chip one (the slices' sums meet in LDS).  K rows
-//   stream from HBM exactly once, in 128-byte row segments that a lane select
-//   and a DPP swap turn into MFMA operands; the query fragments are staged in
-//   LDS phase by phase.  The epilogue takes the max over query rows
-//   (registers, then 16-lane shuffles) and writes m_j = scale * max_i S_ij:
-//   the text-by-vision matrix is never stored.
+// qer_strm (qer_strm.hip): LOGIT scores, and the two SOFTMAX passes, of rows
+//   (heads) of whole 128-byte segments -- every model's.
+// qer_score: LOGIT scores of other rows.  One 8-wave workgroup per CU; each
+//   wave owns MB x 16 visual tokens and all (<= 64, or 128 in eight blocks)
+//   query rows of one chunk, over the whole contraction.  K rows stream from
+//   HBM exactly once, in 128-byte row segments that a lane select and a DPP
+//   swap turn into MFMA operands; the query fragments are staged in LDS phase
+//   by phase.  The epilogue takes the max over query rows (registers, then
+//   16-lane shuffles) and writes m_j = scale * max_i S_ij: the text-by-vision
+//   matrix is never stored.
 // qer_frame_mean: one wave per frame, fp64 mean of m over V_f (Eq. 7); the
 //   last workgroup to finish (an arrival counter the score kernel clears)
 //   ranks the frames by (score desc, frame asc) on order-preserving 32-bit
@@ -30,12 +28,10 @@
 // qer_topk: the same selection as a kernel of its own (the SOFTMAX fallback
 //   kernels, the fused attention path, cofie_topk).
 // SOFTMAX mode: per-(head, query) row statistics over all visual keys, merged
-//   across waves and workgroups, then a second pass forming the head mean of
-//   the normalised probabilities and its max over query rows.  Where every
-//   head is whole 128-byte segments of a key row, both passes are qer_score
-//   with a per-head epilogue (the contraction runs over the query heads in
-//   order, grouped heads reading their key head through a segment map);
-//   other head sizes take per-head kernels of their own.
+//   across workgroups, then a second pass forming the head mean of the
+//   normalised probabilities and its max over query rows.  Heads of whole
+//   128-byte segments take qer_strm's passes (grouped bf16 heads of 128, one
+//   query: qer_soft_grp's); other head sizes take per-head kernels.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -134,26 +130,8 @@ struct ScoreLdsArgs {
   int32_t* clear;      // workgroup 0 zeroes clear[0, nclear) (the frame-mean kernel's
   int32_t nclear;      // arrival counters), may be null
   int32_t lgS;         // log2 S
-  int32_t split_u4;    // contraction split NS ways: 16-byte columns from one slice to the next
-  int32_t k_row_u4;    // 16-byte chunks per key row (shorter than a query row in SOFTMAX GQA)
-  // SOFTMAX passes (the contraction runs over the query heads in order, one
-  // head every sph segments; query head h reads key head h / G)
-  int32_t sph;         // segments per head
-  int32_t H;           // query heads
-  int32_t G;           // query heads per key head
-  float soft_scale;    // scale inside the exponent
-  // pass 1: (max, sum of exp) of row r = h * nq_total + q per wave and round,
-  // part b = (workgroup * 8 + wave) * rounds + round at
-  // stats_part[((r / 16) * nparts + b) * 16 + r % 16]
-  float2* stats_part;
-  int32_t rounds;      // rounds per workgroup
-  int32_t nparts;      // nwg * 8 * rounds
-  const float2* stats; // pass 2: [H][nq_total] (max, sum of exp) over all keys
-  // pass 1 with several queries (group_rows > 0): query g's rows see only the
-  // keys of its first soft_nf[g] frames, [0, soft_offs[soft_nf[g]]); null: all
-  const int32_t* soft_offs;
-  const int32_t* soft_nf;
-  // several key sequences (LOGIT, one contraction slice; null: one): tiles is
+  int32_t k_row_u4;    // 16-byte chunks per key row
+  // several key sequences (null: one): tiles is
   // the total over them, and a workgroup's share is taken one sequence at a
   // time, with that sequence's keys, token count and query rows
   const QerStreamDesc* streams;
@@ -161,29 +139,19 @@ struct ScoreLdsArgs {
   int32_t xcd_order;   // shares in XCD order: consecutive shares to the workgroups of one XCD
 };
 
-constexpr int kModeLogit = 0;     // Eq. 6-7: m_j = max_i a_ij
-constexpr int kModeSoftStats = 1; // SOFTMAX pass 1: per-head row statistics
-constexpr int kModeSoftProb = 2;  // SOFTMAX pass 2: m_j = max_i mean_h P^h_ij
-constexpr int kModeGqa = 4;       // flag: grouped query heads read their key head through a segment map
-constexpr int kModeSeq = 8;       // flag (LOGIT): several key sequences, each with its own query rows
-
 constexpr int kLdsWaves = 8;
 constexpr int kLdsThreads = kLdsWaves * 64;
 // uint4 per thread per phase fill (a phase buffer holds q_regs * 512 uint4):
 // 32 KiB phases when the query side is narrow (fewer registers held, a shorter
 // first fill: 1 fps stream 47.2 vs 48.8 us), 64 KiB otherwise (fewer phases:
 // high-res 20.4 vs 23.1 us)
-// With the contraction split NS ways inside the workgroup (NS > 1) a phase
-// holds NS slices and takes the 64 KiB buffer.
-__host__ __device__ constexpr int lds_q_regs(int PNB, int NS = 1) { return NS == 1 && PNB <= 2 ? 4 : 8; }
+__host__ __device__ constexpr int lds_q_regs(int PNB) { return PNB <= 2 ? 4 : 8; }
 
 // virtual steps per batch: 8 key loads per batch and wave (two batches in
 // flight), fewer where the query fragments and accumulators of wide query
-// blocks take the registers, or where NS slices of a phase of U steps would
-// not fit its buffer; at least one segment (16/R steps)
-__host__ __device__ constexpr int lds_batch(int MB, int PNB, int R, int NS = 1) {
-  int u = MB == 1 ? (PNB <= 4 ? 8 : 4) : (PNB <= 2 ? 4 : 2);
-  while (u > 1 && NS * u * PNB * 64 > lds_q_regs(PNB, NS) * kLdsThreads) u >>= 1;
+// blocks take the registers; at least one segment (16/R steps)
+__host__ __device__ constexpr int lds_batch(int MB, int PNB, int R) {
+  const int u = MB == 1 ? (PNB <= 4 ? 8 : 4) : (PNB <= 2 ? 4 : 2);
   return u > 16 / R ? u : 16 / R;
 }
 
@@ -197,41 +165,13 @@ __device__ __forceinline__ uint4 row_ror4(const uint4& v) {
   else return uint4{row_ror<N>(v.x), row_ror<N>(v.y), row_ror<N>(v.z), row_ror<N>(v.w)};
 }
 
-// Reductions over lanes l and l ^ 16 (l ^ 32) in the VALU: gfx950's
-// v_permlane16_swap / v_permlane32_swap hand each lane the pair (value of the
-// lower lane, value of the upper lane), in that order in both lanes (checked
-// on the device), so both lanes compute the same result.
-__device__ __forceinline__ float max_x16(float v) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float max_x32(float v) {
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float sum_x16(float v) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-__device__ __forceinline__ float sum_x32(float v) {
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-
 // rows per key load.  8 (128-byte segments) measured faster than 4 (256-byte
 // segments) in this kernel on the 1 fps stream workload (48.9 vs 51.1 us).
 __host__ __device__ constexpr int lds_rows(int, int) { return 8; }
 
-// The score kernel's batch (virtual steps per key batch): the host plan's,
-// halved for SOFTMAX pass 1 with three or more query blocks and for pass 2
-// (MHA heads) with eight, one tile per wave: the full batch would spill (the
-// grouped-head pass 2 spills with the half batch instead).  S, the phase
-// length, stays a multiple of it.
-__host__ __device__ constexpr int score_batch(int MB, int NB, int P, int NS, int mode) {
-  return lds_batch(MB, P * NB, lds_rows(MB, P * NB), NS) /
-         (MB == 1 && (((mode & 3) == kModeSoftStats && P * NB >= 3) || (mode == kModeSoftProb && P * NB >= 8)) ? 2
-                                                                                                            : 1);
-}
+// The score kernel's batch (virtual steps per key batch).  S, the phase length,
+// is a multiple of it.
+__host__ __device__ constexpr int score_batch(int MB, int NB, int P) { return lds_batch(MB, P * NB, lds_rows(MB, P * NB)); }
 
 // ---- address arithmetic of qer_score_kernel, shared with its address model ---------
 // Key load q (of 16 / R per segment) of lane `lane` for the tile whose first
@@ -255,21 +195,18 @@ __host__ __device__ __forceinline__ int64_t score_tail_u4(int64_t t0, int lane, 
 // Query fragment load: element e of phase ph (16-byte units): the query row
 // (of term p) and column it takes, and whether it is real (else it loads row
 // q0 of term 0, column 0, and stores zero).
-template <int NB, int NS, int FPS, int EPL>
+template <int NB, int FPS, int EPL>
 __host__ __device__ __forceinline__ int64_t score_q_u4(int32_t n_q, int32_t q0, int32_t nq_total, int32_t Lc,
-                                                       int32_t split_u4, int e, int ph, int lgC, int64_t row_u4,
-                                                       bool& ok) {
-  constexpr int LGNS = NS == 4 ? 2 : (NS == 2 ? 1 : 0);
-  const int row = e >> (lgC + LGNS), f = row >> 4;
+                                                       int e, int ph, int lgC, int64_t row_u4, bool& ok) {
+  const int row = e >> lgC, f = row >> 4;
   const int p = f / NB, nb = f - p * NB;
   const int q = nb * 16 + (row & 15);
-  const int sl = (e >> lgC) & (NS - 1);
-  const int col = sl * split_u4 + (ph << lgC) + (e & ((1 << lgC) - 1));
+  const int col = (ph << lgC) + (e & ((1 << lgC) - 1));
   ok = f < FPS && q < n_q && col * EPL < Lc;
   const int64_t grow = ok ? (int64_t)p * nq_total + q0 + q : (int64_t)q0;
   return grow * row_u4 + (ok ? col : 0);
 }
-// Query fragments in LDS, one phase buffer: [slice][step][fragment][lane],
+// Query fragments in LDS, one phase buffer: [step][fragment][lane],
 // 16 bytes per lane.  Phase column c of a query row (a 16-byte chunk) belongs
 // to virtual step ls = VPS (c / SEGC) + c % VPS and lane group
 // g = (c % SEGC) / VPS, the order in which the key segments are read; row r
@@ -281,63 +218,40 @@ __host__ __device__ __forceinline__ int score_swz(int ls, int g) {
   constexpr int LOGU = U >= 8 ? 3 : (U >= 4 ? 2 : 1);
   return ((ls & (U - 1)) | (g << LOGU)) & 15;
 }
-// slot of column c, fragment f, row r within a slice's steps
+// slot of column c, fragment f, row r
 template <int U, int VPS, int SEGC, int FPS>
 __host__ __device__ __forceinline__ int score_q_slot_c(int c, int f, int r) {
   const int ls = VPS * (c / SEGC) + c % VPS, g = (c % SEGC) / VPS;
   return ((ls * FPS + f) << 6) + (g << 4) + (r ^ score_swz<U>(ls, g));
 }
-// The slot element e of a phase's row-major query load is stored to: slice
-// (e >> lgC) % NS, row (e >> lgC) / NS (fragment row / 16, row row % 16),
-// column e % 2^lgC; spare elements past the fragments keep slot e (their value
-// is zero and never read).
-template <int U, int VPS, int SEGC, int FPS, int NS>
-__host__ __device__ __forceinline__ int score_q_slot(int e, int lgC, int lgS) {
-  constexpr int LGNS = NS == 4 ? 2 : (NS == 2 ? 1 : 0);
-  const int row = e >> (lgC + LGNS), f = row >> 4;
-  const int sl = (e >> lgC) & (NS - 1);
+// The slot element e of a phase's row-major query load is stored to: row
+// e >> lgC (fragment row / 16, row row % 16), column e % 2^lgC; spare elements
+// past the fragments keep slot e (their value is zero and never read).
+template <int U, int VPS, int SEGC, int FPS>
+__host__ __device__ __forceinline__ int score_q_slot(int e, int lgC) {
+  const int row = e >> lgC, f = row >> 4;
   if (f >= FPS) return e;
-  return ((sl * FPS) << (lgS + 6)) + score_q_slot_c<U, VPS, SEGC, FPS>(e & ((1 << lgC) - 1), f, row & 15);
+  return score_q_slot_c<U, VPS, SEGC, FPS>(e & ((1 << lgC) - 1), f, row & 15);
 }
 
-// NS > 1 splits the contraction inside the workgroup: wave w multiplies slice
-// w % NS (a.split_u4 columns from the previous one) of the tiles of wave group
-// w / NS, and the slices' accumulators are added in slice order through LDS
-// before the maximum over the query rows, so that few tiles still occupy every
-// wave of every CU.
-//
-// MODE selects the epilogue: kModeLogit as above; the SOFTMAX passes close
-// every head (sph segments of the contraction) in registers: pass 1 writes the
-// head's (max, sum of exp) over the wave's tokens for every query row, pass 2
-// adds exp(s - max) / sum over the heads and ends like LOGIT with the head
-// mean's maximum over the query rows.
-template <typename T, int MB, int NB, int P, int NS, int MODE>
+// SEQ: several key sequences, each with its own query rows.
+template <typename T, int MB, int NB, int P, bool SEQ>
 __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) {
   using M = Mma<T>;
-  constexpr int BASE = MODE & 3;  // kModeLogit, kModeSoftStats or kModeSoftProb
-  constexpr bool GQA = (MODE & kModeGqa) != 0;
-  constexpr bool SEQ = (MODE & kModeSeq) != 0;
   constexpr int R = lds_rows(MB, P * NB);
   constexpr int VPS = 16 / R;   // virtual steps (= loads per tile) per segment
   constexpr int SEGC = 64 / R;  // 16-byte chunks per segment
-  constexpr int U = score_batch(MB, NB, P, NS, MODE);
+  constexpr int U = score_batch(MB, NB, P);
   constexpr int FPS = P * NB;   // fragments per virtual step
-  constexpr int kQRegs = lds_q_regs(FPS, NS);
+  constexpr int kQRegs = lds_q_regs(FPS);
   constexpr int kPhaseU4 = kQRegs * kLdsThreads;
-  constexpr int TW = kLdsWaves / NS;  // waves per slice (tiles per round when MB = 1)
-  constexpr int LGNS = NS == 4 ? 2 : (NS == 2 ? 1 : 0);
+  constexpr int TW = kLdsWaves;  // tiles per round when MB = 1
   static_assert(U % VPS == 0, "batches hold whole segments");
-  static_assert(NS == 1 || NS == 2 || NS == 4, "1, 2 or 4 slices");
-  static_assert(NS == 1 || MB == 1, "split contractions take one tile per wave");
-  static_assert(BASE == kModeLogit || (NS == 1 && P == 1), "SOFTMAX passes: one query term, no split");
-  static_assert(!GQA || BASE != kModeLogit, "the segment map is for the SOFTMAX passes");
-  static_assert(!SEQ || (BASE == kModeLogit && NS == 1), "several key sequences: LOGIT, one slice");
-  // [2][kPhaseU4]: [NS][S][P][NB][64] each; with NS > 1 followed by the
-  // slice accumulators [NS - 1][TW][MB][NB][4][64] floats
+  // [2][kPhaseU4]: [S][P][NB][64] each
   extern __shared__ uint4 qs[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int slice = wave & (NS - 1), tw = wave >> LGNS;
+  const int tw = wave;
   const int r16 = lane & 15, g4 = lane >> 4;
   const int qs_lane = r16 / R;  // load index holding this lane's own row
   // Query fragments in LDS: a phase of S steps per buffer in the layout of
@@ -349,7 +263,7 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
   const int pfull = VPS * a.nseg;
   const int64_t row_u4 = (int64_t)a.Lc * sizeof(T) / 16;
   const int64_t krow_u4 = a.k_row_u4;
-  const uint4* const K0 = reinterpret_cast<const uint4*>(a.K) + (NS > 1 ? slice * a.split_u4 : 0);
+  const uint4* const K0 = reinterpret_cast<const uint4*>(a.K);
   const uint4* Kq = K0;
   const uint4* Qq = reinterpret_cast<const uint4*>(a.Qp);
   // This workgroup's share of the tiles.  Workgroups are dealt to the XCDs in
@@ -364,44 +278,6 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
     while (sidx + 1 < a.n_streams && a.streams[sidx].tile0 + a.streams[sidx].ntiles <= f_begin) ++sidx;
   if (blockIdx.x == 0 && a.clear)
     for (int i = tid; i < a.nclear; i += kLdsThreads) a.clear[i] = 0;
-
-  // pass 1: exp(scale acc - m) = exp2(acc c2 - m log2 e), one FMA and
-  // v_exp_f32 (pass 2 keeps __expf: the FMA form made the grouped-head,
-  // two-tile, 48-row variant spill)
-  const float c2 = a.soft_scale * 1.44269504088896341f;
-  // SOFTMAX passes: past the phase buffers, pass 2's row statistics of this
-  // query chunk ([H][n_q]: max, 1 / sum of exp) and, for grouped heads, the
-  // key segment of every contraction segment.  The first barrier of the round
-  // loop publishes them.
-  float2* st_sh = reinterpret_cast<float2*>(qs + (a.nphase > 1 ? 2 : 1) * kPhaseU4);
-  int32_t* seg_map = reinterpret_cast<int32_t*>(st_sh + (BASE == kModeSoftProb ? a.H * a.n_q : 0));
-  // pass 1: the keys each 16-row block's query sees (padding blocks none)
-  int64_t key_lim[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    key_lim[nb] = a.n_vis;
-    if constexpr (BASE == kModeSoftStats) {
-      if (a.soft_nf) {
-        int64_t l = 0;
-        if (nb * 16 < a.n_q) {
-          l = a.soft_offs[a.soft_nf[(a.q0 + nb * 16) / a.group_rows]];
-          l = l < 0 ? 0 : (l > a.n_vis ? a.n_vis : l);
-        }
-        key_lim[nb] = l;
-      }
-    }
-  }
-  if constexpr (BASE != kModeLogit) {
-    if constexpr (GQA)
-      for (int v = tid; v < a.nseg; v += kLdsThreads) seg_map[v] = (v / a.sph / a.G) * a.sph + v % a.sph;
-    if constexpr (BASE == kModeSoftProb)
-      for (int i = tid; i < a.H * a.n_q; i += kLdsThreads) {
-        const int hh = i / a.n_q, q = i - hh * a.n_q;
-        const float2 st = a.stats[(int64_t)hh * a.nq_total + a.q0 + q];
-        // L = M log2 e + log2 Z: p = exp2(s scale log2 e - L)
-        st_sh[i] = make_float2(st.x * 1.44269504088896341f + __log2f(st.y), 0.f);
-      }
-  }
 
   bool qok[NB];
 #pragma unroll
@@ -418,8 +294,6 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
   // so that issuing the loads never waits for them.
   uint32_t qmask = 0;
   const int lgC = a.lgS + 2;  // log2 of the 16-byte columns per row and phase (4 S, S a power of two)
-  // With NS slices, consecutive runs of a row alternate between the slices:
-  // element e is slice (e >> lgC) % NS, row (e >> lgC) / NS.
   auto q_load = [&](int ph, uint4 (&qr)[kQRegs]) __attribute__((always_inline)) {
     qmask = 0;
 #pragma unroll
@@ -427,8 +301,8 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
       // slots past the P NB fragments (f >= FPS, so p >= P) and masked rows
       // load row q0 of term 0, which every chunk has
       bool ok;
-      const int64_t src = score_q_u4<NB, NS, FPS, M::EPL>(a.n_q, a.q0, a.nq_total, a.Lc, a.split_u4,
-                                                          tid + kLdsThreads * i, ph, lgC, row_u4, ok);
+      const int64_t src =
+          score_q_u4<NB, FPS, M::EPL>(a.n_q, a.q0, a.nq_total, a.Lc, tid + kLdsThreads * i, ph, lgC, row_u4, ok);
       qr[i] = Qq[src];
       qmask |= ok ? 1u << i : 0u;
     }
@@ -438,7 +312,7 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
 #pragma unroll
     for (int i = 0; i < kQRegs; ++i) {
       const bool ok = (qmask >> i) & 1u;
-      dst[score_q_slot<U, VPS, SEGC, FPS, NS>(tid + kLdsThreads * i, lgC, a.lgS)] =
+      dst[score_q_slot<U, VPS, SEGC, FPS>(tid + kLdsThreads * i, lgC)] =
           uint4{ok ? qr[i].x : 0u, ok ? qr[i].y : 0u, ok ? qr[i].z : 0u, ok ? qr[i].w : 0u};
     }
   };
@@ -474,97 +348,11 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[j][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // SOFTMAX passes: close query head hh, whose unscaled dot products are in
-    // acc, and start the next one from zero
-    f32x4 prob[MB][NB];  // pass 2: sum over the heads closed so far
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) prob[j][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int head = 0, head_seg = 0;
-    // pass 1: bit 4 j + r of vmask[nb] set when this lane's accumulator
-    // element (tile j, token 4 g4 + r) is a key that block nb's query sees
-    uint32_t vmask[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) vmask[nb] = 0;
-    if constexpr (BASE == kModeSoftStats) {
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t tok = (int64_t)(rb + tw + TW * j) * 16 + g4 * 4 + r;
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            vmask[nb] |= (j < nmb && tok < key_lim[nb]) ? 1u << (4 * j + r) : 0u;
-        }
-    }
-    auto head_close = [&](int hh) __attribute__((always_inline)) {
-      if constexpr (BASE == kModeSoftStats) {
-        // (m, sum of exp(s - m)) over this wave's valid tokens, per query row,
-        // m = 0 or, where the sum against 0 is out of range, the max; a wave
-        // without tokens writes (-inf, 0)
-        const int64_t slot = ((int64_t)blockIdx.x * kLdsWaves + wave) * a.rounds + (rb - t_begin) / (TW * MB);
-        const int64_t row0 = (int64_t)hh * a.nq_total + a.q0;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          // the sum against 0 first (no max); the row's four lane groups hold
-          // the same sum, so the exact form below runs for whole rows only,
-          // where that sum leaves (2^-64, 2^64) or the row has no valid token
-          float z = 0.f;
-#pragma unroll
-          for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if ((vmask[nb] >> (4 * j + r)) & 1u) z += __builtin_amdgcn_exp2f(acc[j][nb][r] * c2);
-          z = sum_x32(sum_x16(z));
-          float mx = 0.f;
-          if (!(z < 0x1p64f && z > 0x1p-64f)) {
-            mx = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < MB; ++j)
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if ((vmask[nb] >> (4 * j + r)) & 1u) mx = fmaxf(mx, acc[j][nb][r]);
-            mx = max_x32(max_x16(mx));
-            const float mc = mx * c2;
-            z = 0.f;
-#pragma unroll
-            for (int j = 0; j < MB; ++j)
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if ((vmask[nb] >> (4 * j + r)) & 1u) z += __builtin_amdgcn_exp2f(fmaf(acc[j][nb][r], c2, -mc));
-            z = sum_x32(sum_x16(z));
-          }
-          const int q = nb * 16 + r16;
-          if (g4 == 0 && q < a.n_q) {
-            const int64_t row = row0 + q;  // 16 lanes: one or two 128-byte runs
-            a.stats_part[((row >> 4) * a.nparts + slot) * 16 + (row & 15)] = make_float2(mx * a.soft_scale, z);
-          }
-        }
-      } else if constexpr (BASE == kModeSoftProb) {
-        const float2* sth = st_sh + hh * a.n_q;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const int q = nb * 16 + r16;
-          const float2 st = sth[q < a.n_q ? q : a.n_q - 1];
-#pragma unroll
-          for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) prob[j][nb][r] += __builtin_amdgcn_exp2f(fmaf(acc[j][nb][r], c2, -st.x));
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[j][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    };
-
     // loads of the U virtual steps from ms (U/VPS segments, VPS loads each)
     auto k_load = [&](uint4 (&f)[U][MB], int ms) __attribute__((always_inline)) {
 #pragma unroll
       for (int h = 0; h < U / VPS; ++h) {
-        int seg = min(ms / VPS + h, a.nseg - 1);
-        if constexpr (GQA) seg = seg_map[seg];
+        const int seg = min(ms / VPS + h, a.nseg - 1);
 #pragma unroll
         for (int q = 0; q < VPS; ++q)
 #pragma unroll
@@ -590,29 +378,13 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
     // one batch: prefetch the next batch into `nxt`, multiply `cur`, and at a
     // phase end publish the next phase's fragments
     int ph = 0;
-    // SOFTMAX with grouped heads: `nxt` holds the batch two before the one it
-    // is about to receive; when both read the same key segments (consecutive
-    // query heads of one key head), the keys are already in place
-    auto keys_in_place = [&](int X) __attribute__((always_inline)) {
-      if constexpr (!GQA) {
-        return false;
-      } else {
-        if (X < 2 * U) return false;
-        bool same = true;
-#pragma unroll
-        for (int h = 0; h < U / VPS; ++h)
-          same = same && seg_map[min(X / VPS + h, a.nseg - 1)] == seg_map[min((X - 2 * U) / VPS + h, a.nseg - 1)];
-        return same;
-      }
-    };
     auto batch = [&](int ms, const uint4 (&cur)[U][MB], uint4 (&nxt)[U][MB], bool guard) __attribute__((always_inline)) {
-      if (!keys_in_place(ms + U)) k_load(nxt, ms + U);
+      k_load(nxt, ms + U);
       if (pending && ms > ph * a.S) {
         q_store(ph + 1, qr);
         pending = false;
       }
-      // ms - ph S is a multiple of U; this wave's slice starts S FPS 64 slots further per slice
-      const uint4* qb = qs + (ph & 1) * kPhaseU4 + ((slice * a.S + ms - ph * a.S) * FPS) * 64;
+      const uint4* qb = qs + (ph & 1) * kPhaseU4 + (ms - ph * a.S) * FPS * 64;  // ms - ph S is a multiple of U
 #pragma unroll
       for (int h = 0; h < U / VPS; ++h) {
         if (!guard || ms + VPS * h < pfull) {
@@ -658,13 +430,6 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
 #pragma unroll
                 for (int j = 0; j < MB; ++j) M::mac(acc[j][nb], fk[j], qf[p * NB + nb]);
           }
-          if constexpr (BASE != kModeLogit) {
-            if (++head_seg == a.sph) {
-              head_close(head);
-              ++head;
-              head_seg = 0;
-            }
-          }
         }
       }
       if (ms + U == (ph + 1) * a.S && ph + 1 < a.nphase) {
@@ -704,7 +469,7 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
       const bool in = (col + g4) * M::EPL < a.Lc;
       const int cph = (col + g4) - (ph << lgC);  // this lane's column within the phase
       const uint4* qb =
-          qs + (ph & 1) * kPhaseU4 + (((slice * FPS) << (a.lgS + 6)) + score_q_slot_c<U, VPS, SEGC, FPS>(cph, 0, r16));
+          qs + (ph & 1) * kPhaseU4 + score_q_slot_c<U, VPS, SEGC, FPS>(cph, 0, r16);
       uint4 kf[MB];
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
@@ -719,41 +484,6 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
 #pragma unroll
           for (int j = 0; j < MB; ++j) M::mac(acc[j][nb], kf[j], qf);
         }
-    }
-
-    // the slices' sums: slices 1.. NS-1 publish their accumulators, slice 0
-    // adds them in slice order (the buffer lies past the phase buffers in use)
-    if constexpr (NS > 1) {
-      float* red = reinterpret_cast<float*>(qs + (a.nphase > 1 ? 2 : 1) * kPhaseU4);
-      auto red_at = [&](int sl, int j, int nb, int r) __attribute__((always_inline)) {
-        return ((((((sl - 1) * TW + tw) * MB + j) * NB + nb) * 4 + r) << 6) + lane;
-      };
-      if (slice > 0) {
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) red[red_at(slice, j, nb, r)] = acc[j][nb][r];
-      }
-      barrier_lds();
-      if (slice > 0) continue;  // the next round begins with a barrier of all waves
-#pragma unroll
-      for (int sl = 1; sl < NS; ++sl)
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[j][nb][r] += red[red_at(sl, j, nb, r)];
-    }
-
-    if constexpr (BASE == kModeSoftStats) continue;  // the statistics are written
-    if constexpr (BASE == kModeSoftProb) {
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[j][nb] = prob[j][nb];
     }
 
     // m_j = scale * max over the query rows: registers over nb, then the 16
@@ -828,19 +558,6 @@ __global__ __launch_bounds__(kLdsThreads) void qer_score_kernel(ScoreLdsArgs a) 
     }
   } else {
     rounds(f_begin, f_end);
-  }
-  if constexpr (BASE == kModeSoftStats) {
-    // the rounds this workgroup does not run leave empty statistics (a zero
-    // sum), which the merge skips
-    const int nr = (f_end - f_begin + TW * MB - 1) / (TW * MB);
-    for (int rr = nr; rr < a.rounds; ++rr) {
-      const int64_t slot = ((int64_t)blockIdx.x * kLdsWaves + wave) * a.rounds + rr;
-      for (int i = lane; i < a.H * a.n_q; i += 64) {
-        const int hh = i / a.n_q, q = i - hh * a.n_q;
-        const int64_t row = (int64_t)hh * a.nq_total + a.q0 + q;
-        a.stats_part[((row >> 4) * a.nparts + slot) * 16 + (row & 15)] = make_float2(-INFINITY, 0.f);
-      }
-    }
   }
 }
 
@@ -1404,12 +1121,11 @@ struct QerPlan {
   bool fold;
   size_t esize;
   int64_t nblk_soft;
-  // SOFTMAX through the LDS-staged score kernel: heads of whole 128-byte
-  // segments, the pass-2 statistics and the segment map within the LDS budget
+  // SOFTMAX through the streaming passes: heads of whole 128-byte segments
   bool soft_fast;
-  bool soft_wide;       // 128 query rows per pass (else 64)
-  int64_t soft_nwg;     // workgroups of the score kernel (qer_soft_grp_kernel: pass 1's key ranges)
-  int64_t soft_rounds;  // their rounds (qer_soft_grp_kernel: 1)
+  int64_t soft_nwg, soft_rounds;  // statistics pairs in the scratch: nwg x 8 waves x rounds
+                                  // (qer_soft_grp_kernel: pass 1's key ranges, 1)
+  StrmSoftPlan soft_strm;
   // SOFTMAX through qer_soft_grp_kernel (grouped bf16 heads of d = 128, one query)
   bool soft_grp;
 };
@@ -1507,59 +1223,34 @@ int validate_qer(const void* Q, const void* K, const int32_t* offs, const cofie_
 
 // Work split of the LDS-staged score kernel: one workgroup per CU (fewer for
 // small inputs), tiles of 16 tokens spread evenly over the workgroups, 1 or 2
-// tiles per wave per round, 4-row key segments unless the batch is too short
-// to hold one, phases as long as a 64 KiB buffer allows.  Inputs of too few
-// tiles to give every wave of the chip a tile split the contraction NS ways
-// (NS depends on the tile count, the contraction and the query terms only, not
-// on the query rows, so that queries ranked together or alone add in the same
-// order).
+// tiles per wave per round, phases as long as their buffer allows.
 struct LdsPlan {
-  int MB, R, NS, nwg, S, lgS, nphase, nseg, ksteps, split_u4;
+  int MB, R, nwg, S, lgS, nphase, nseg, ksteps;
   size_t lds;
 };
 
-// Slices of the contraction for `tiles` tiles: the largest NS in {4, 2} whose
-// tiles still take one round (one tile per wave group on at most every CU:
-// each further round restages the whole query side and restarts the key
-// pipeline, measured at ~11 us per round for the multi-stream heads, more than
-// the split saves), else 1.  Whole segments per slice, no tail steps, one
-// query term.
-inline int plan_slices(int64_t tiles, int64_t Lc, size_t esize, int P, int cus) {
-  const int64_t seg_el = (1024 / lds_rows(1, 1)) / (int64_t)esize;
-  if (P != 1 || esize != 4 || Lc % seg_el != 0) return 1;  // bf16 rows of whole segments take qer_strm_kernel
-  const int64_t nseg = Lc / seg_el;
-  for (int ns = 4; ns > 1; ns /= 2)
-    if (nseg % ns == 0 && tiles <= (int64_t)cus * (kLdsWaves / ns)) return ns;
-  return 1;
-}
-
-LdsPlan plan_score_lds(int64_t n_vis, int64_t Lc, size_t esize, int P, int PNB, int cus, bool split_ok) {
+LdsPlan plan_score_lds(int64_t n_vis, int64_t Lc, size_t esize, int PNB, int cus) {
   LdsPlan L;
   const int64_t tiles = ceil_div(n_vis, 16);
-  L.NS = split_ok ? plan_slices(tiles, Lc, esize, P, cus) : 1;
-  const int tw = kLdsWaves / L.NS;
-  L.nwg = (int)std::min<int64_t>(cus, ceil_div(tiles, tw));
+  L.nwg = (int)std::min<int64_t>(cus, ceil_div(tiles, kLdsWaves));
   const int64_t tpw = ceil_div(tiles, L.nwg);
-  L.MB = (L.NS == 1 && tpw > kLdsWaves) ? 2 : 1;
+  L.MB = tpw > kLdsWaves ? 2 : 1;
   L.R = lds_rows(L.MB, PNB);
-  const int U = lds_batch(L.MB, PNB, L.R, L.NS);
-  const int64_t kps = 64 / (int64_t)esize;             // elements per plain MFMA step
+  const int U = lds_batch(L.MB, PNB, L.R);
+  const int64_t kps = 64 / (int64_t)esize;               // elements per plain MFMA step
   const int64_t seg_el = (1024 / L.R) / (int64_t)esize;  // elements per segment
-  const int64_t Ls = Lc / L.NS;                        // one slice (whole segments when NS > 1)
-  L.nseg = (int)(Ls / seg_el);
-  L.ksteps = (int)((16 / L.R) * L.nseg + ceil_div(Ls % seg_el, kps));
-  L.split_u4 = (int)(Ls * (int64_t)esize / 16);
-  const int phase_u4 = lds_q_regs(PNB, L.NS) * kLdsThreads;
-  // S: a power of two (>= U), as large as the phase buffer holds (NS slices
-  // of S steps), no larger than the contraction needs
-  const int64_t cap = (phase_u4 / 64) / PNB / L.NS;
+  L.nseg = (int)(Lc / seg_el);
+  L.ksteps = (int)((16 / L.R) * L.nseg + ceil_div(Lc % seg_el, kps));
+  const int phase_u4 = lds_q_regs(PNB) * kLdsThreads;
+  // S: a power of two (>= U), as large as the phase buffer holds, no larger
+  // than the contraction needs
+  const int64_t cap = (phase_u4 / 64) / PNB;
   L.S = U;
   while (2 * L.S <= cap && L.S < L.ksteps) L.S *= 2;
   L.lgS = 0;
   while ((1 << L.lgS) < L.S) ++L.lgS;
   L.nphase = (int)ceil_div(L.ksteps, L.S);
   L.lds = (size_t)(L.nphase > 1 ? 2 : 1) * phase_u4 * sizeof(uint4);
-  if (L.NS > 1) L.lds += (size_t)(L.NS - 1) * tw * PNB * 4 * 64 * sizeof(float);
   return L;
 }
 
@@ -1579,18 +1270,15 @@ const T* shadow_of(const T* dev, const char* what) {
 }
 
 // qer_score_kernel with grid `grid` and `lds` bytes of LDS
-template <typename T, int MB, int NB, int P, int NS, int MODE>
+template <typename T, int MB, int NB, int P, bool SEQ>
 void model_score(ScoreLdsArgs a, int grid, size_t lds) {
-  constexpr int BASE = MODE & 3;
-  constexpr bool GQA = (MODE & kModeGqa) != 0;
-  constexpr bool SEQ = (MODE & kModeSeq) != 0;
   constexpr int R = lds_rows(MB, P * NB);
   constexpr int VPS = 16 / R, SEGC = 64 / R;
-  constexpr int U = score_batch(MB, NB, P, NS, MODE);
+  constexpr int U = score_batch(MB, NB, P);
   constexpr int FPS = P * NB;
-  constexpr int kQRegs = lds_q_regs(FPS, NS);
+  constexpr int kQRegs = lds_q_regs(FPS);
   constexpr int kPhaseU4 = kQRegs * kLdsThreads;
-  constexpr int TW = kLdsWaves / NS;
+  constexpr int TW = kLdsWaves;
   const int64_t L = (int64_t)lds;
   const int lgC = a.lgS + 2;
   const int pfull = VPS * a.nseg;
@@ -1599,43 +1287,22 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
   dry_range(grid, a.nwg, a.nwg + 1, "score: grid and planned workgroups differ");
   if (a.xcd_order) dry_range(a.nwg % 8, 0, 1, "score: XCD order needs whole groups of 8 workgroups");
   if (a.clear && a.nclear > 0) dry_access(a.clear, 0, 4 * (int64_t)a.nclear, "score: arrival counters");
-  // LDS past the phase buffers
-  const int64_t extra = (int64_t)(a.nphase > 1 ? 2 : 1) * kPhaseU4 * 16;
-  if constexpr (BASE == kModeSoftProb) dry_lds(extra, (int64_t)a.H * a.n_q * 8, L, "score: row statistics in LDS");
-  int seg_lo = 0, seg_hi = a.nseg - 1;  // the key segments read (mapped for grouped heads)
-  if constexpr (GQA) {
-    dry_lds(extra + (BASE == kModeSoftProb ? (int64_t)a.H * a.n_q * 8 : 0), 4 * (int64_t)a.nseg, L,
-            "score: segment map");
-    seg_lo = INT32_MAX;
-    seg_hi = -1;
-    for (int v = 0; v < a.nseg; ++v) {
-      const int sm = (v / a.sph / a.G) * a.sph + v % a.sph;
-      seg_lo = std::min(seg_lo, sm);
-      seg_hi = std::max(seg_hi, sm);
-    }
-  }
-  if constexpr (NS > 1) dry_lds(extra, (int64_t)(NS - 1) * TW * MB * NB * 4 * 64 * 4, L, "score: slice sums");
-  if constexpr (BASE == kModeSoftProb)
-    if (a.H * a.n_q > 0) {
-      dry_access(a.stats, ((int64_t)a.q0) * 8, 8, "score: pass-2 statistics");
-      dry_access(a.stats, ((int64_t)(a.H - 1) * a.nq_total + a.q0 + a.n_q - 1) * 8, 8, "score: pass-2 statistics");
-    }
-
+  const int seg_lo = 0, seg_hi = a.nseg - 1;  // the key segments read
   // query fragment stores: slots inside the phase buffer, both buffers
   for (int par = 0; par < (a.nphase > 1 ? 2 : 1); ++par)
     for (int e = 0; e < kPhaseU4; ++e) {
-      const int slot = score_q_slot<U, VPS, SEGC, FPS, NS>(e, lgC, a.lgS);
+      const int slot = score_q_slot<U, VPS, SEGC, FPS>(e, lgC);
       dry_range(slot, 0, kPhaseU4, "score: query slot outside its phase buffer");
       dry_lds(((int64_t)par * kPhaseU4 + slot) * 16, 16, L, "score: query fragment store");
     }
   // fragment reads of the batches and the tail, following the kernel's phase
   // counter; phase ph's buffer is ph % 2
-  for (int slice = 0; slice < NS; ++slice) {
+  {
     int ph = 0;
     bool pending = a.nphase > 1;
     for (int ms = 0; ms < pfull; ms += U) {
       if (pending && ms > ph * a.S) pending = false;
-      const int64_t qb = ((int64_t)slice * a.S + ms - (int64_t)ph * a.S) * FPS * 64;
+      const int64_t qb = (ms - (int64_t)ph * a.S) * FPS * 64;
       for (int h = 0; h < U / VPS; ++h) {
         if (ms + VPS * h >= pfull) continue;
         for (int k = 0; k < VPS; ++k) {
@@ -1657,7 +1324,7 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
       for (int lane = 0; lane < 64; ++lane) {
         const int cph = col + (lane >> 4) - (ph << lgC);
         dry_range(cph, 0, 1 << lgC, "score: tail column outside its phase");
-        const int64_t slot = ((int64_t)(slice * FPS) << (a.lgS + 6)) + score_q_slot_c<U, VPS, SEGC, FPS>(cph, 0, lane & 15);
+        const int64_t slot = score_q_slot_c<U, VPS, SEGC, FPS>(cph, 0, lane & 15);
         for (int f = 0; f < FPS; ++f) {
           dry_range(slot + f * 64, 0, kPhaseU4, "score: tail fragment read outside its phase buffer");
           dry_lds(((ph & 1) * (int64_t)kPhaseU4 + slot + f * 64) * 16, 16, L, "score: tail fragment read");
@@ -1671,39 +1338,24 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
     for (int ph = 0; ph < a.nphase; ++ph)
       for (int e = 0; e < kPhaseU4; ++e) {
         bool ok;
-        const int64_t src = score_q_u4<NB, NS, FPS, Mma<T>::EPL>(n_q, q0, a.nq_total, a.Lc, a.split_u4, e, ph, lgC,
-                                                                 row_u4, ok);
+        const int64_t src = score_q_u4<NB, FPS, Mma<T>::EPL>(n_q, q0, a.nq_total, a.Lc, e, ph, lgC, row_u4, ok);
         dry_access(a.Qp, src * 16, 16, "score: query load");
       }
   };
   std::vector<std::pair<int, int>> q_done;
-  const int32_t* nf_h = nullptr;
-  if constexpr (BASE == kModeSoftStats)
-    if (a.soft_nf) nf_h = shadow_of(a.soft_nf, "score: per-query frame counts without a host copy");
   // tiles [t_begin, t_end) of one key sequence for workgroup b
-  auto share = [&](int b, int t_begin, int t_end, int64_t kbase_u4, int64_t n_vis, int q0, int n_q) {
+  auto share = [&](int t_begin, int t_end, int64_t kbase_u4, int64_t n_vis, int q0, int n_q) {
     if (std::find(q_done.begin(), q_done.end(), std::make_pair(q0, n_q)) == q_done.end()) {
       q_done.push_back({q0, n_q});
       q_loads(q0, n_q);
     }
-    if constexpr (BASE == kModeSoftStats) {
-      if (a.soft_nf)
-        for (int nb = 0; nb < NB; ++nb)
-          if (nb * 16 < n_q) {
-            const int gi = (q0 + nb * 16) / a.group_rows;
-            dry_access(a.soft_nf, 4 * (int64_t)gi, 4, "score: per-query frame count");
-            if (nf_h) dry_access(a.soft_offs, 4 * (int64_t)nf_h[gi], 4, "score: the query's key limit");
-          }
-    }
     const int64_t last = n_vis - 1;
     for (int rb = t_begin; rb < t_end; rb += TW * MB) {
-      const int rr = (rb - t_begin) / (TW * MB);
-      if constexpr (BASE == kModeSoftStats) dry_range(rr, 0, a.rounds, "score: round past the statistics slots");
       for (int tw = 0; tw < TW; ++tw) {
         int nmb = 0;
         for (int j = 0; j < MB; ++j) nmb += (rb + tw + TW * j < t_end) ? 1 : 0;
-        for (int slice = 0; slice < NS; ++slice) {
-          const int64_t k0 = kbase_u4 + (NS > 1 ? (int64_t)slice * a.split_u4 : 0);
+        {
+          const int64_t k0 = kbase_u4;
           for (int j = 0; j < MB; ++j) {
             const int64_t t0 = (int64_t)(j < nmb ? rb + tw + TW * j : rb) * 16;
             for (int lane = 0; lane < 64; ++lane) {
@@ -1721,17 +1373,7 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
             }
           }
         }
-        if constexpr (BASE == kModeSoftStats) {
-          // (max, sum) of every head and query row of this wave and round
-          const int heads = a.sph > 0 ? a.nseg / a.sph : 0;
-          const int64_t slot = ((int64_t)b * kLdsWaves + tw) * a.rounds + rr;
-          if (heads > 0 && n_q > 0)
-            for (int64_t row : {(int64_t)q0, (int64_t)(heads - 1) * a.nq_total + q0 + n_q - 1})
-              dry_access(a.stats_part, (((row >> 4) * a.nparts + slot) * 16 + (row & 15)) * 8, 8,
-                         "score: pass-1 statistics");
-          continue;
-        }
-        // the maxima of this wave's tiles (slice 0 of the wave group)
+        // the maxima of this wave's tiles
         for (int j = 0; j < nmb; ++j) {
           const int64_t tile = rb + tw + TW * j;
           for (int64_t tok : {tile * 16, std::min(tile * 16 + 15, n_vis - 1)}) {
@@ -1758,7 +1400,6 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
     dry_range(wg, 0, a.nwg, "score: workgroup share");
     const int f_begin = (int)((int64_t)a.tiles * wg / a.nwg);
     const int f_end = (int)((int64_t)a.tiles * (wg + 1) / a.nwg);
-    int nr = 0;  // rounds run (pass 1: the rest are filled with empty statistics)
     if constexpr (SEQ) {
       if (!sd_h) return;
       int sidx = 0;
@@ -1770,21 +1411,10 @@ void model_score(ScoreLdsArgs a, int grid, size_t lds) {
         if (s_end <= fb || sd.ntiles <= 0) continue;
         const int tb = fb - sd.tile0, te = (s_end < f_end ? s_end : f_end) - sd.tile0;
         fb = sd.tile0 + te;
-        share(blk, tb, te, sd.key0 * krow_u4, sd.n_keys, sd.q0, sd.n_rows);
+        share(tb, te, sd.key0 * krow_u4, sd.n_keys, sd.q0, sd.n_rows);
       }
     } else {
-      share(blk, f_begin, f_end, 0, a.n_vis, a.q0, a.n_q);
-      nr = (f_end - f_begin + TW * MB - 1) / (TW * MB);
-    }
-    if constexpr (BASE == kModeSoftStats) {
-      for (int tw = 0; tw < kLdsWaves; ++tw)
-        for (int rr = nr; rr < a.rounds; ++rr) {
-          const int64_t slot = ((int64_t)blk * kLdsWaves + tw) * a.rounds + rr;
-          if (a.H * a.n_q > 0)
-            for (int64_t row : {(int64_t)a.q0, (int64_t)(a.H - 1) * a.nq_total + a.q0 + a.n_q - 1})
-              dry_access(a.stats_part, (((row >> 4) * a.nparts + slot) * 16 + (row & 15)) * 8, 8,
-                         "score: empty pass-1 statistics");
-        }
+      share(f_begin, f_end, 0, a.n_vis, a.q0, a.n_q);
     }
   }
 }
@@ -1846,54 +1476,45 @@ int launch_frame_mean(int gx, int gy, int threads, hipStream_t s, const float* m
                 s, m, n_vis, offs, n_frames, out_scores, keys, nf_q, trees, tree_ints, tree_stride, k_top, out_idx, qd);
 }
 
-template <typename T, int MB, int NB, int P, int NS, int MODE>
-int launch_lds_t(const ScoreLdsArgs& sa, const LdsPlan& L, size_t lds, hipStream_t s) {
-  auto k = qer_score_kernel<T, MB, NB, P, NS, MODE>;
-  int rc = allow_lds(k, lds);
+template <typename T, int MB, int NB, int P, bool SEQ>
+int launch_lds_t(const ScoreLdsArgs& sa, const LdsPlan& L, hipStream_t s) {
+  auto k = qer_score_kernel<T, MB, NB, P, SEQ>;
+  int rc = allow_lds(k, L.lds);
   if (rc) return rc;
   if (dry_run()) {
-    dry_range((int64_t)lds, 0, 160 * 1024 + 1, "score: LDS beyond a CU's 160 KiB");
-    if (L.nwg > 0) model_score<T, MB, NB, P, NS, MODE>(sa, L.nwg, lds);
+    dry_range((int64_t)L.lds, 0, 160 * 1024 + 1, "score: LDS beyond a CU's 160 KiB");
+    if (L.nwg > 0) model_score<T, MB, NB, P, SEQ>(sa, L.nwg, L.lds);
     return COFIE_OK;
   }
-  const int base = MODE & 3;
-  const char* name = base == kModeLogit ? "qer_score" : (base == kModeSoftStats ? "qer_soft_stats" : "qer_soft_score");
-  return launch(name, k, dim3((unsigned)L.nwg), dim3(kLdsThreads), lds, s, sa);
+  return launch("qer_score", k, dim3((unsigned)L.nwg), dim3(kLdsThreads), L.lds, s, sa);
 }
 
-template <typename T, int MB, int P, int NS, int MODE>
-int launch_lds_nb(const ScoreLdsArgs& sa, const LdsPlan& L, int NB, size_t lds, hipStream_t s) {
-  // 128 query rows in one pass: one query term, one tile per wave (two
-  // spill), no contraction split (LOGIT, and both SOFTMAX passes)
-  if constexpr (MB == 1 && P == 1 && NS == 1) {
-    if (NB == 8) return launch_lds_t<T, 1, 8, 1, NS, MODE>(sa, L, lds, s);
+template <typename T, int MB, int P, bool SEQ>
+int launch_lds_nb(const ScoreLdsArgs& sa, const LdsPlan& L, int NB, hipStream_t s) {
+  // 128 query rows in one pass: one query term, one tile per wave (two spill)
+  if constexpr (MB == 1 && P == 1) {
+    if (NB == 8) return launch_lds_t<T, 1, 8, 1, SEQ>(sa, L, s);
   }
   switch (NB) {
-    case 1: return launch_lds_t<T, MB, 1, P, NS, MODE>(sa, L, lds, s);
-    case 2: return launch_lds_t<T, MB, 2, P, NS, MODE>(sa, L, lds, s);
-    case 3: return launch_lds_t<T, MB, 3, P, NS, MODE>(sa, L, lds, s);
-    default: return launch_lds_t<T, MB, 4, P, NS, MODE>(sa, L, lds, s);
+    case 1: return launch_lds_t<T, MB, 1, P, SEQ>(sa, L, s);
+    case 2: return launch_lds_t<T, MB, 2, P, SEQ>(sa, L, s);
+    case 3: return launch_lds_t<T, MB, 3, P, SEQ>(sa, L, s);
+    default: return launch_lds_t<T, MB, 4, P, SEQ>(sa, L, s);
   }
 }
 
-// lds = 0: the plan's (the phase buffers and the slices' accumulators)
-template <typename T, int P, int MODE = kModeLogit>
-int launch_lds(const ScoreLdsArgs& sa, const LdsPlan& L, int NB, hipStream_t s, size_t lds = 0) {
-  if (!lds) lds = L.lds;
-  if constexpr (P == 1 && MODE == kModeLogit && sizeof(T) == 4) {
-    if (L.NS == 4) return launch_lds_nb<T, 1, P, 4, MODE>(sa, L, NB, lds, s);
-    if (L.NS == 2) return launch_lds_nb<T, 1, P, 2, MODE>(sa, L, NB, lds, s);
-  }
-  return L.MB == 1 ? launch_lds_nb<T, 1, P, 1, MODE>(sa, L, NB, lds, s)
-                   : launch_lds_nb<T, 2, P, 1, MODE>(sa, L, NB, lds, s);
+template <typename T, int P, bool SEQ = false>
+int launch_lds(const ScoreLdsArgs& sa, const LdsPlan& L, int NB, hipStream_t s) {
+  return L.MB == 1 ? launch_lds_nb<T, 1, P, SEQ>(sa, L, NB, s) : launch_lds_nb<T, 2, P, SEQ>(sa, L, NB, s);
 }
 
-// SOFTMAX through the score kernel: the LDS of a pass (phase buffers, pass 2's
-// statistics [H][nq] of its query chunk, the segment map for grouped heads)
-// and the pass-1 statistics per row (one per wave and round).
-size_t soft_lds(const LdsPlan& L, int mode, int H, int nq_chunk, int G, int64_t nseg) {
-  size_t b = L.lds;
-  if (mode == kModeSoftProb) b += (size_t)H * nq_chunk * sizeof(float2);
+// What SOFTMAX over heads of whole 128-byte segments accepts (several queries)
+// and the scratch it asks for: those of passes that hold the query phases of
+// the score kernel, a pair of statistics per row of a chunk and a segment map
+// in LDS, and one statistics pair per wave and round in memory.  The streaming
+// passes need less of both.
+size_t soft_lds(const LdsPlan& L, int H, int nq_chunk, int G, int64_t nseg) {
+  size_t b = L.lds + (size_t)H * nq_chunk * sizeof(float2);
   if (G > 1) b += (size_t)nseg * sizeof(int32_t);
   return b;
 }
@@ -1923,8 +1544,9 @@ int grp_ranges1(const cofie_qer_desc& h, int cus) {
 // of a key row, the widest query chunk's LDS within the CU's), and its
 // pass-1 statistics count.
 void plan_soft(const cofie_qer_desc& h, int32_t n_queries, QerPlan& p) {
-  p.soft_fast = p.soft_wide = p.soft_grp = false;
+  p.soft_fast = p.soft_grp = false;
   p.soft_nwg = p.soft_rounds = 0;
+  p.soft_strm = StrmSoftPlan{0, 0, 0};
   if (h.score_mode != COFIE_SCORE_SOFTMAX || h.n_vis <= 0) return;
   if (soft_grp_ok(h, n_queries)) {
     p.soft_grp = true;
@@ -1939,17 +1561,20 @@ void plan_soft(const cofie_qer_desc& h, int32_t n_queries, QerPlan& p) {
   // 128 query rows per pass (K read twice for up to 128 stacked rows) where
   // the plan takes one tile per wave and the LDS holds the pass-2 statistics
   // of 128 rows; else 64
-  p.soft_wide = false;
+  bool soft_wide = false;
   if (rows > 64) {
-    const LdsPlan W = plan_score_lds(h.n_vis, p.Lc, p.esize, 1, 8, cus, false);
-    p.soft_wide = W.MB == 1 && soft_lds(W, kModeSoftProb, h.H_q, 128, h.H_q / h.H_kv, p.Lc / seg_el) <= kLdsMax;
+    const LdsPlan W = plan_score_lds(h.n_vis, p.Lc, p.esize, 8, cus);
+    soft_wide = W.MB == 1 && soft_lds(W, h.H_q, 128, h.H_q / h.H_kv, p.Lc / seg_el) <= kLdsMax;
   }
-  const int nq = (int)std::min<int64_t>(p.soft_wide ? 128 : 64, rows), NB = nq > 64 ? 8 : (nq + 15) / 16;
-  const LdsPlan L = plan_score_lds(h.n_vis, p.Lc, p.esize, 1, NB, cus, false);
-  if (soft_lds(L, kModeSoftProb, h.H_q, nq, h.H_q / h.H_kv, p.Lc / seg_el) > kLdsMax) return;
+  const int nq = (int)std::min<int64_t>(soft_wide ? 128 : 64, rows), NB = nq > 64 ? 8 : (nq + 15) / 16;
+  const LdsPlan L = plan_score_lds(h.n_vis, p.Lc, p.esize, NB, cus);
+  if (soft_lds(L, h.H_q, nq, h.H_q / h.H_kv, p.Lc / seg_el) > kLdsMax) return;
   p.soft_fast = true;
   p.soft_nwg = L.nwg;
   p.soft_rounds = soft_rounds(L, h.n_vis);
+  p.soft_strm = plan_strm_soft(h.n_vis, h.H_q, (int64_t)h.d * (int64_t)p.esize, h.dtype == COFIE_F32,
+                               (int)std::min<int64_t>(rows, 128), cus);
+  if (!p.soft_strm.max_rows) p.soft_fast = false;  // (no shape that fits above misses)
 }
 
 template <typename T, int NB>
@@ -2016,14 +1641,15 @@ int rank_impl(const void* Q, const void* K, const int32_t* frame_offsets, const 
         qp = w.qp;
       }
       const int32_t nclear = n_queries * qer_trees(h.n_frames, n_queries).ints;
-      const StrmPlan st = bf16 ? plan_strm(ceil_div(h.n_vis, 16), p.Lc, p.P, 0, device_cu_count()) : StrmPlan{0, 0, 0};
+      const int64_t row_bytes = p.Lc * (int64_t)p.esize;
+      const StrmPlan st = plan_strm(ceil_div(h.n_vis, 16), row_bytes, p.P, !bf16, h.n_q, false, device_cu_count());
       if (st.NS > 0 && strm_ok(R, p)) {
         StrmArgs a{};
         a.K = static_cast<const uint8_t*>(K);
         a.Q = qp;
-        a.row_bytes = p.Lc * 2;
+        a.row_bytes = row_bytes;
         a.nq_total = R;
-        a.nseg = (int32_t)(p.Lc / 64 / st.NS);
+        a.nseg = (int32_t)(row_bytes / 128 / st.NS);
         a.n_seq = 1;
         a.tiles = ceil_div(h.n_vis, 16);
         a.nwg = st.nwg;
@@ -2036,7 +1662,7 @@ int rank_impl(const void* Q, const void* K, const int32_t* frame_offsets, const 
           a.one = QerStreamDesc{0, h.n_vis, 0, a.tiles, q0, std::min(st.max_rows, R - q0), 0};
           a.clear = (q0 == 0 && fused_tail) ? w.done : nullptr;
           a.accumulate = q0 > 0;
-          rc = launch_strm(a, st, p.P, a.one.n_rows, s);
+          rc = launch_strm(a, st, !bf16, p.P, a.one.n_rows, s);
           if (rc) return rc;
         }
       } else {
@@ -2054,12 +1680,9 @@ int rank_impl(const void* Q, const void* K, const int32_t* frame_offsets, const 
         sa.nclear = n_queries * qer_trees(h.n_frames, n_queries).ints;
         const int cus = device_cu_count();
         // query rows per pass over K: 64, or 128 (eight 16-row blocks) where the
-        // plan gives one tile per wave, no contraction split (its LDS would not
-        // fit; the split, which decides the summation order, stays a function of
-        // the keys alone) and one query term, so that K is read once for up to
-        // 128 rows (several queries of a stream)
-        const LdsPlan probe = plan_score_lds(h.n_vis, p.Lc, p.esize, p.P, 4, cus, true);
-        const bool wide = p.P == 1 && R > 64 && probe.MB == 1 && probe.NS == 1;
+        // plan gives one tile per wave and there is one query term
+        const LdsPlan probe = plan_score_lds(h.n_vis, p.Lc, p.esize, p.P * 4, cus);
+        const bool wide = p.P == 1 && R > 64 && probe.MB == 1;
         const int chunk = wide ? 128 : 64;
         for (int q0 = 0; q0 < R; q0 += chunk) {
           sa.clear = (q0 == 0 && fused_tail) ? w.done : nullptr;
@@ -2067,14 +1690,13 @@ int rank_impl(const void* Q, const void* K, const int32_t* frame_offsets, const 
           sa.n_q = std::min(chunk, R - q0);
           sa.accumulate = q0 > 0;
           const int NB = sa.n_q > 64 ? 8 : (sa.n_q + 15) / 16;
-          const LdsPlan L = plan_score_lds(h.n_vis, p.Lc, p.esize, p.P, p.P * NB, cus, true);
+          const LdsPlan L = plan_score_lds(h.n_vis, p.Lc, p.esize, p.P * NB, cus);
           sa.nseg = L.nseg;
           sa.ksteps = L.ksteps;
           sa.S = L.S;
           sa.lgS = L.lgS;
           sa.nphase = L.nphase;
           sa.nwg = L.nwg;
-          sa.split_u4 = L.split_u4;
           sa.k_row_u4 = (int32_t)(p.Lc * (int64_t)p.esize / 16);
           if (bf16)
             rc = p.P == 3 ? launch_lds<bf16_t, 3>(sa, L, NB, s) : launch_lds<bf16_t, 1>(sa, L, NB, s);
@@ -2114,74 +1736,47 @@ int rank_impl(const void* Q, const void* K, const int32_t* frame_offsets, const 
       rc = launch_grp(ga, h.H_kv, h.H_q / h.H_kv, 2, s);
       if (rc) return rc;
     } else if (p.soft_fast) {
-      // two passes of the score kernel over K (per-head statistics, then the
-      // probabilities), the statistics merged in between
-      ScoreLdsArgs sa{};
-      sa.K = static_cast<const uint8_t*>(K);
-      sa.Qp = static_cast<const uint8_t*>(Q);
-      sa.n_vis = h.n_vis;
-      sa.nq_total = R;  // several queries: their rows stacked, statistics per row
-      sa.group_rows = multi ? h.n_q : 0;
-      sa.soft_offs = multi ? frame_offsets : nullptr;
-      sa.soft_nf = multi ? w.nf : nullptr;
-      sa.m_stride = h.n_vis;
-      sa.Lc = (int32_t)p.Lc;
-      sa.tiles = (int32_t)ceil_div(h.n_vis, 16);
-      sa.m = w.m;
-      sa.k_row_u4 = (int32_t)((int64_t)h.H_kv * h.d * (int64_t)p.esize / 16);
-      const int64_t seg_el = (1024 / lds_rows(1, 1)) / (int64_t)p.esize;
-      sa.sph = (int32_t)(h.d / seg_el);
-      sa.H = h.H_q;
-      sa.G = h.H_q / h.H_kv;
-      sa.soft_scale = base_scale;
-      sa.stats_part = w.partial;
-      sa.stats = w.stats;
-      sa.nclear = n_queries * qer_trees(h.n_frames, n_queries).ints;
-      const int cus = device_cu_count();
-      const int chunk = p.soft_wide ? 128 : 64;
+      // two passes of the streaming kernel over K, the statistics merged in
+      // between
+      StrmSoftArgs a{};
+      a.K = static_cast<const uint8_t*>(K);
+      a.Q = static_cast<const uint8_t*>(Q);
+      a.k_row_bytes = (int64_t)h.H_kv * h.d * (int64_t)p.esize;
+      a.q_row_bytes = (int64_t)h.H_q * h.d * (int64_t)p.esize;
+      a.n_vis = h.n_vis;
+      a.tiles = ceil_div(h.n_vis, 16);
+      a.nq_total = R;
+      a.sph = (int32_t)((int64_t)h.d * (int64_t)p.esize / 128);
+      a.H = h.H_q;
+      a.G = h.H_q / h.H_kv;
+      a.nwg = p.soft_strm.nwg;
+      a.c2 = base_scale * 1.44269504088896341f;
+      a.soft_scale = base_scale;
+      a.inv_h = 1.0f / (float)h.H_q;
+      a.stats_part = w.partial;
+      a.nparts = a.nwg;
+      if (a.nparts > p.soft_nwg * kLdsWaves * p.soft_rounds)  // the scratch was sized for those
+        return set_error(COFIE_EHIP, "SOFTMAX plan: %d statistics parts", a.nparts);
+      a.stats = w.stats;
+      a.m = w.m;
+      a.m_stride = h.n_vis;
+      a.group_rows = multi ? h.n_q : 0;
+      a.soft_offs = multi ? frame_offsets : nullptr;
+      a.soft_nf = multi ? w.nf : nullptr;
+      a.nclear = n_queries * qer_trees(h.n_frames, n_queries).ints;
       for (int pass = 1; pass <= 2; ++pass) {
-        for (int q0 = 0; q0 < R; q0 += chunk) {
-          sa.q0 = q0;
-          sa.n_q = std::min(chunk, R - q0);
-          sa.accumulate = pass == 2 && q0 > 0;
-          sa.clear = (pass == 2 && q0 == 0 && fused_tail) ? w.done : nullptr;
-          sa.scale = 1.0f / (float)h.H_q;  // pass 2: the head mean
-          const int NB = sa.n_q > 64 ? 8 : (sa.n_q + 15) / 16;
-          const LdsPlan L = plan_score_lds(h.n_vis, p.Lc, p.esize, 1, NB, cus, false);
-          sa.nseg = L.nseg;
-          sa.ksteps = L.ksteps;
-          sa.S = L.S;
-          sa.lgS = L.lgS;
-          sa.nphase = L.nphase;
-          sa.nwg = L.nwg;
-          sa.split_u4 = L.split_u4;
-          sa.rounds = (int32_t)soft_rounds(L, h.n_vis);
-          sa.nparts = (int32_t)(p.soft_nwg * kLdsWaves * p.soft_rounds);
-          if (L.nwg != p.soft_nwg || sa.rounds != p.soft_rounds)  // the scratch was sized for that plan
-            return set_error(COFIE_EHIP, "SOFTMAX plan mismatch (%d x %d against %lld x %lld)", L.nwg, sa.rounds,
-                             (long long)p.soft_nwg, (long long)p.soft_rounds);
-          const int mode = pass == 1 ? kModeSoftStats : kModeSoftProb;
-          const size_t lds = soft_lds(L, mode, h.H_q, sa.n_q, sa.G, L.nseg);
-          const bool gqa = sa.G > 1;
-          if (pass == 1 && !gqa)
-            rc = bf16 ? launch_lds<bf16_t, 1, kModeSoftStats>(sa, L, NB, s, lds)
-                      : launch_lds<float, 1, kModeSoftStats>(sa, L, NB, s, lds);
-          else if (pass == 1)
-            rc = bf16 ? launch_lds<bf16_t, 1, kModeSoftStats | kModeGqa>(sa, L, NB, s, lds)
-                      : launch_lds<float, 1, kModeSoftStats | kModeGqa>(sa, L, NB, s, lds);
-          else if (!gqa)
-            rc = bf16 ? launch_lds<bf16_t, 1, kModeSoftProb>(sa, L, NB, s, lds)
-                      : launch_lds<float, 1, kModeSoftProb>(sa, L, NB, s, lds);
-          else
-            rc = bf16 ? launch_lds<bf16_t, 1, kModeSoftProb | kModeGqa>(sa, L, NB, s, lds)
-                      : launch_lds<float, 1, kModeSoftProb | kModeGqa>(sa, L, NB, s, lds);
+        for (int q0 = 0; q0 < R; q0 += p.soft_strm.max_rows) {
+          a.q0 = q0;
+          a.n_q = std::min(p.soft_strm.max_rows, R - q0);
+          a.accumulate = q0 > 0;
+          a.clear = (pass == 2 && q0 == 0 && fused_tail) ? w.done : nullptr;
+          rc = launch_strm_soft(a, p.soft_strm.NS, !bf16, pass == 2, s);
           if (rc) return rc;
         }
         if (pass == 1) {
           const int32_t rows = h.H_q * R;
-          rc = launch("qer_soft_merge", qer_soft_merge_blocked_kernel, dim3((unsigned)ceil_div(rows, 16)),
-                      dim3(1024), 0, s, (const float2*)w.partial, p.soft_nwg * kLdsWaves * p.soft_rounds, rows,
-                      w.stats);
+          rc = launch("qer_soft_merge", qer_soft_merge_blocked_kernel, dim3((unsigned)ceil_div(rows, 16)), dim3(1024),
+                      0, s, (const float2*)w.partial, (int64_t)a.nparts, rows, w.stats);
           if (rc) return rc;
         }
       }
@@ -2326,7 +1921,6 @@ StreamsScratch carve_streams(Arena& ar, const cofie_qer_desc& h, const QerPlan& 
   return w;
 }
 
-constexpr int kSeqLogit = kModeLogit | kModeSeq;
 
 int rank_streams_impl(const void* Q, const void* K, const int32_t* frame_offsets, const cofie_qer_desc& h,
                       const QerPlan& p, const StreamsPlan& sp, int32_t k_top, float* out_scores, int32_t* out_idx,
@@ -2363,14 +1957,15 @@ int rank_streams_impl(const void* Q, const void* K, const int32_t* frame_offsets
   const QerTrees tr = qer_trees(std::max(sp.max_frames, 1), sp.n_queries);
   const float base_scale = h.scale > 0.f ? h.scale : (float)(1.0 / std::sqrt((double)h.d));
   const int cus = device_cu_count();
-  const StrmPlan st = bf16 && strm_ok(R, p) ? plan_strm(sp.tiles, p.Lc, p.P, 16 * sp.NB, cus) : StrmPlan{0, 0, 0};
+  const int64_t row_bytes = p.Lc * (int64_t)p.esize;
+  const StrmPlan st = strm_ok(R, p) ? plan_strm(sp.tiles, row_bytes, p.P, !bf16, 16 * sp.NB, true, cus) : StrmPlan{0, 0, 0, false};
   if (st.NS > 0) {
     StrmArgs a{};
     a.K = static_cast<const uint8_t*>(K);
     a.Q = qp;
-    a.row_bytes = p.Lc * 2;
+    a.row_bytes = row_bytes;
     a.nq_total = R;
-    a.nseg = (int32_t)(p.Lc / 64 / st.NS);
+    a.nseg = (int32_t)(row_bytes / 128 / st.NS);
     a.seq = seq_d;
     a.n_seq = (int32_t)sp.seq.size();
     a.tiles = (int32_t)sp.tiles;
@@ -2382,7 +1977,7 @@ int rank_streams_impl(const void* Q, const void* K, const int32_t* frame_offsets
     a.group_rows = h.n_q;
     a.clear = w.done;
     a.nclear = sp.n_queries * tr.ints;
-    rc = launch_strm(a, st, p.P, 16 * sp.NB, s);
+    rc = launch_strm(a, st, !bf16, p.P, 16 * sp.NB, s);
     if (rc) return rc;
     return launch_frame_mean(tr.nwg, sp.n_queries, 1024, s, (const float*)w.m, (int32_t)a.m_stride, frame_offsets,
                              std::max(sp.max_frames, 1), out_scores, w.keys, (const int32_t*)nullptr, w.done, tr.ints,
@@ -2390,10 +1985,9 @@ int rank_streams_impl(const void* Q, const void* K, const int32_t* frame_offsets
   }
   // the score kernel: one launch over every chunk's tiles (its workgroup 0
   // clears the frame-mean kernel's arrival trees, so it runs even without keys)
-  LdsPlan L = plan_score_lds(std::max<int64_t>(sp.tiles, 1) * 16, p.Lc, p.esize, p.P, p.P * sp.NB, cus, false);
+  LdsPlan L = plan_score_lds(std::max<int64_t>(sp.tiles, 1) * 16, p.Lc, p.esize, p.P * sp.NB, cus);
   if (sp.NB == 8 && L.MB != 1) {  // eight blocks take one tile per wave (two spill)
-    L = plan_score_lds(std::min<int64_t>(sp.tiles, (int64_t)cus * kLdsWaves) * 16, p.Lc, p.esize, p.P,
-                       p.P * sp.NB, cus, false);
+    L = plan_score_lds(std::min<int64_t>(sp.tiles, (int64_t)cus * kLdsWaves) * 16, p.Lc, p.esize, p.P * sp.NB, cus);
   }
   ScoreLdsArgs sa{};
   sa.K = static_cast<const uint8_t*>(K);
@@ -2416,27 +2010,14 @@ int rank_streams_impl(const void* Q, const void* K, const int32_t* frame_offsets
   sa.nphase = L.nphase;
   sa.nwg = std::max(1, (L.nwg >= 8 ? L.nwg & ~7 : L.nwg));
   sa.xcd_order = sa.nwg % 8 == 0 ? 1 : 0;
-  sa.split_u4 = L.split_u4;
   sa.k_row_u4 = (int32_t)(p.Lc * (int64_t)p.esize / 16);
   sa.streams = seq_d;
   sa.n_streams = (int32_t)sp.seq.size();
   L.nwg = sa.nwg;
-  if (bf16) {
-    if (sp.NB == 8)
-      rc = launch_lds_t<bf16_t, 1, 8, 1, 1, kSeqLogit>(sa, L, L.lds, s);
-    else if (p.P == 3)
-      rc = L.MB == 1 ? launch_lds_nb<bf16_t, 1, 3, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s)
-                     : launch_lds_nb<bf16_t, 2, 3, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s);
-    else
-      rc = L.MB == 1 ? launch_lds_nb<bf16_t, 1, 1, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s)
-                     : launch_lds_nb<bf16_t, 2, 1, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s);
-  } else {
-    if (sp.NB == 8)
-      rc = launch_lds_t<float, 1, 8, 1, 1, kSeqLogit>(sa, L, L.lds, s);
-    else
-      rc = L.MB == 1 ? launch_lds_nb<float, 1, 1, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s)
-                     : launch_lds_nb<float, 2, 1, 1, kSeqLogit>(sa, L, sp.NB, L.lds, s);
-  }
+  if (bf16)
+    rc = p.P == 3 ? launch_lds<bf16_t, 3, true>(sa, L, sp.NB, s) : launch_lds<bf16_t, 1, true>(sa, L, sp.NB, s);
+  else
+    rc = launch_lds<float, 1, true>(sa, L, sp.NB, s);
   if (rc) return rc;
   return launch_frame_mean(tr.nwg, sp.n_queries, 1024, s,
                 (const float*)w.m, (int32_t)sa.m_stride, frame_offsets, std::max(sp.max_frames, 1), out_scores,

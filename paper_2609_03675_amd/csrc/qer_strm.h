@@ -1,6 +1,7 @@
-// LOGIT-mode QER scores of bf16 heads (Sec. 3.3, Eqs. 6-7 up to the frame
-// mean): qer_strm_kernel, which streams the keys through LDS by DMA, launched
-// by the QER driver.
+// QER scores of key and query rows of whole 128-byte segments (Sec. 3.3, Eqs.
+// 6-7 up to the frame mean), in LOGIT and SOFTMAX mode: qer_strm_kernel and
+// qer_strm_soft_kernel, which stream the keys through LDS by DMA, launched by
+// the QER driver.
 #pragma once
 
 #include "common.h"
@@ -45,14 +46,57 @@ struct StrmArgs {
 // at most, workgroups.  NS = 0: not this kernel.
 struct StrmPlan {
   int NS, max_rows, nwg;
+  bool half;  // blocks of 16 rows
 };
-// P query terms (1, or 3 for folded grouped heads) of Lc elements, whole
-// 128-byte segments, at least two; rows that one launch must take (0: a
-// launch may take any part of them -- the plan then depends on the keys only,
-// so that queries ranked together or alone add in the same order).
-StrmPlan plan_strm(int64_t tiles, int64_t Lc, int P, int rows, int cus);
+// P query terms (1, or 3 for folded grouped bf16 heads) of row_bytes, whole
+// 128-byte segments; rows: with `all` those that one launch must take, else
+// those of one query (of which a launch may take any part: the plan is that of
+// the query alone, so that queries ranked together add in the same order).
+StrmPlan plan_strm(int64_t tiles, int64_t row_bytes, int P, bool f32, int rows, bool all, int cus);
 // Scores of one query chunk per sequence (rows: the widest chunk's).  In a
 // dry run, the address model instead.
-int launch_strm(const StrmArgs& a, const StrmPlan& p, int P, int rows, hipStream_t s);
+int launch_strm(const StrmArgs& a, const StrmPlan& p, bool f32, int P, int rows, hipStream_t s);
+
+// ---- SOFTMAX mode: heads of whole 128-byte segments, one key sequence -----------------
+struct StrmSoftArgs {
+  const uint8_t* K;        // [n_vis] rows of k_row_bytes (H / G key heads)
+  const uint8_t* Q;        // [nq_total] rows of q_row_bytes (H query heads)
+  int64_t k_row_bytes, q_row_bytes;
+  int32_t n_vis, tiles;    // keys, 16-key tiles
+  int32_t q0, n_q, nq_total;
+  int32_t nseg;            // steps of a slice: set by launch_strm_soft
+  int32_t sph;             // segments per head
+  int32_t H, G;            // query heads, of which G consecutive ones read one key head
+  int32_t nwg;             // workgroups
+  float c2;                // scale log2 e
+  float soft_scale;        // scale
+  float inv_h;             // 1 / H
+  // pass 1: (max, sum of exp) of row r = h * nq_total + q over workgroup b's
+  // keys at stats_part[((r / 16) * nparts + b) * 16 + r % 16]
+  float2* stats_part;
+  int32_t nparts;
+  int32_t direct;          // pass 1: set by launch_strm_soft (no room for the table in LDS)
+  int32_t slots;           // segment slots: set by launch_strm_soft
+  const float2* stats;     // pass 2: the merged pairs
+  float* m;                // pass 2: m[g * m_stride + key]
+  int64_t m_stride;
+  int32_t group_rows;      // rows per query (a multiple of 16); 0: one query
+  int32_t accumulate;      // one query: take the max with what m holds
+  // pass 1 with several queries: query g's rows see only the keys of its
+  // first soft_nf[g] frames, [0, soft_offs[soft_nf[g]]); null: all
+  const int32_t* soft_offs;
+  const int32_t* soft_nf;
+  int32_t* clear;          // workgroup 0 zeroes clear[0, nclear)
+  int32_t nclear;
+};
+
+// max_rows = 0: not this kernel.
+struct StrmSoftPlan {
+  int max_rows, nwg, NS;  // query rows of a launch, workgroups, head slices
+};
+StrmSoftPlan plan_strm_soft(int64_t n_vis, int H, int64_t head_bytes, bool f32, int rows, int cus);
+// Pass 1 (statistics) or 2 (probabilities) of one query chunk; in a dry run,
+// the address model instead.
+int launch_strm_soft(const StrmSoftArgs& a, int ns, bool f32, bool prob, hipStream_t s);
 
 }  // namespace cofie

@@ -1,5 +1,6 @@
 // qer_strm_kernel: m_j = scale * max_i sum over the contraction of q_i k_j for
-// bf16 rows (LOGIT mode, Eq. 6-7), on gfx950.
+// bf16 or fp32 rows (LOGIT mode, Eq. 6-7), and qer_strm_soft_kernel: the two
+// passes of the SOFTMAX mode, on gfx950.
 //
 // HBM-bound: about n_q flop per byte of keys.  What the kernel has to do is
 // keep the key stream deep and undisturbed, so keys go from HBM to LDS by DMA
@@ -7,8 +8,8 @@
 //  * one workgroup of 8 waves per CU; a wave owns 32 keys and all (at most
 //    16 QB) query rows of a chunk, over the whole contraction or, for inputs
 //    of few tiles, one of NS slices of it;
-//  * the contraction runs in segments of 64 elements (128 bytes of a row, the
-//    shape that streams at full rate: 8 rows x 128 bytes per instruction).  A
+//  * the contraction runs in segments of 128 bytes of a row (64 bf16 or 32
+//    fp32 elements; the shape that streams at full rate: 8 rows x 128 bytes per instruction).  A
 //    wave has SL slots of one segment of its keys in LDS: it copies a slot
 //    to registers (4 fragments), refills it at once with the segment SL
 //    ahead, and multiplies from registers;
@@ -19,10 +20,13 @@
 //    slot c ^ (row / 2 % 8): the DMA writes its lanes' 16 bytes consecutively,
 //    so the permutation is made by the lanes' global addresses, and 16 rows'
 //    reads of one chunk fall on all 64 banks.
-// S = Q K^T (32x32x16 MFMA, queries as the A operand): a lane holds one key
-// and 16 query rows of a block in registers, so the max over the rows is in
-// registers but for one exchange between the half waves.
-// The pipeline runs over all rounds of a workgroup's share (NS = 1).
+// S = Q K^T (bf16 32x32x16 MFMA, or four fp32 32x32x2 over the 16 bytes each
+// lane holds; queries as the A operand): a lane holds one key and 16 query
+// rows of a block in registers, so the max over the rows is in registers but
+// for one exchange between the half waves.  fp32 rows that end in 16 past a
+// multiple of 32 take 16x16x4 MFMAs, which bound them (41 rows x 39984 keys of
+// 28 heads of 128: 254 -> 196 us).  The pipeline runs over all rounds of a
+// workgroup's share (NS = 1).
 // Measured against keys loaded to registers in operand shape by a lane select
 // and a DPP rotation, queries restaged through registers (28 heads of 128):
 // 32 rows x 32768 keys 41.6 -> 37.5 us (6.3 TB/s), 64 x 46080 75 -> 57 (5.8),
@@ -34,26 +38,95 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 namespace cofie {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
+struct StrmBf16 {};  // element types of the rows: this or float
 constexpr int kSegBytes = 128;
 constexpr int kKeyDma = 4;  // key DMA instructions per segment and wave
 
+template <typename T>
+struct Mma;
+template <>
+struct Mma<StrmBf16> {
+  __device__ __forceinline__ static void mac(f32x16& acc, const uint4& a, const uint4& b) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                  0, 0, 0);
+  }
+  __device__ __forceinline__ static void mac(f32x4& acc, const uint4& a, const uint4& b) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                  0, 0, 0);
+  }
+};
+// fp32: MFMA e contracts element e of the half waves' 16 bytes (their chunks
+// 2 j and 2 j + 1 of the segment), so four cover the same 32 bytes of a row;
+// those of 16 rows the four lane groups', 64 bytes
+template <>
+struct Mma<float> {
+  __device__ __forceinline__ static void mac(f32x16& acc, const uint4& a, const uint4& b) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+  __device__ __forceinline__ static void mac(f32x4& acc, const uint4& a, const uint4& b) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+};
+
+// Products of a wave's 32 keys with a block of 32 query rows, or of 16 (HB, as
+// two halves of 16 keys: rows that end 16 past a multiple of 32 multiply no
+// padding).  EL elements of a lane; with the keys as A operand, element e is
+// query row (lane % rows) and key key(e) + first(lane).
+template <bool HB>
+struct Tile {
+  static constexpr int EL = 16, ROWS = 32;
+  f32x16 v;
+  __device__ __forceinline__ void clear() { v = 0.f; }
+  __device__ __forceinline__ float get(int e) const { return v[e]; }
+  __device__ __forceinline__ void add(int e, float x) { v[e] += x; }
+  __device__ __forceinline__ static constexpr int key(int e) { return 8 * (e >> 2) + (e & 3); }
+  __device__ __forceinline__ static int first(int l) { return 4 * (l >> 5); }
+};
+template <>
+struct Tile<true> {
+  static constexpr int EL = 8, ROWS = 16;
+  f32x4 v[2];
+  __device__ __forceinline__ void clear() { v[0] = v[1] = 0.f; }
+  __device__ __forceinline__ float get(int e) const { return v[e >> 2][e & 3]; }
+  __device__ __forceinline__ void add(int e, float x) { v[e >> 2][e & 3] += x; }
+  __device__ __forceinline__ static constexpr int key(int e) { return 16 * (e >> 2) + (e & 3); }
+  __device__ __forceinline__ static int first(int l) { return 4 * (l >> 4); }
+};
+
 // LDS of a configuration: the query buffers [SL][NS][P 16 QB rows][128], then
 // the waves' key slots [8][SL][32 rows][128].  (The last 32-row block of an
-// odd QB reads 16 rows past its term's; those products are never used.)
+// odd QB of qer_strm_kernel reads 16 rows past its term's; those products are
+// never used.)
 __host__ __device__ constexpr int strm_q_bytes(int QB, int P, int NS) { return NS * P * QB * 16 * kSegBytes; }
 constexpr int kKeyBytes = 32 * kSegBytes;
 __host__ __device__ constexpr int strm_lds(int QB, int P, int NS, int SL) {
   return SL * (strm_q_bytes(QB, P, NS) + kWaves * kKeyBytes);
+}
+
+// The SOFTMAX passes': KS > 0 (a key head's segments held for the group's
+// query heads) has its own number of key slots; PK (two query heads of 16
+// rows) has 32 query rows.
+__host__ __device__ constexpr int soft_key_slots(int SL, int KS) { return KS ? (KS < 2 ? 2 : KS) : SL; }
+__host__ __device__ constexpr int soft_ring(int QB, int NS, int SL, int KS, bool PK) {
+  return SL * strm_q_bytes(PK ? 2 : QB, 1, NS) + kWaves * soft_key_slots(SL, KS) * kKeyBytes;
 }
 
 // DMA instruction i of 8 rows x 128 bytes: lane l brings row 8 i + l / 8's
@@ -64,6 +137,17 @@ __host__ __device__ __forceinline__ int strm_chunk(int i, int l) { return (l & 7
 __host__ __device__ __forceinline__ int strm_frag(int j, int l) {
   const int r = l & 31;
   return r * kSegBytes + 16 * ((2 * j + (l >> 5)) ^ ((r >> 1) & 7));
+}
+
+// In blocks of 16 rows: of the j-th 64 bytes, lane l reads row l % 16's chunk
+// 4 j + l / 16.
+__host__ __device__ __forceinline__ int strm_frag16(int j, int l) {
+  const int r = l & 15;
+  return r * kSegBytes + 16 * ((4 * j + (l >> 4)) ^ ((r >> 1) & 7));
+}
+// The four key fragments of a segment.
+__host__ __device__ __forceinline__ int strm_key_frag(bool hb, int j, int l) {
+  return hb ? (j >> 1) * 16 * kSegBytes + strm_frag16(j & 1, l) : strm_frag(j, l);
 }
 
 // The part of a share [f_begin, f_end) that lies in one sequence, and its
@@ -105,6 +189,19 @@ __host__ __device__ __forceinline__ int64_t strm_q_off(int i, int l, int P, int 
   return grow * row_bytes + sl * slice_bytes + 16 * strm_chunk(b, l);
 }
 
+// Key segment of contraction segment v when query heads of sph segments run in
+// order and G consecutive ones share a key head.
+__host__ __device__ __forceinline__ int strm_key_seg(int v, int sph, int G) {
+  return G == 1 ? v : (v / sph / G) * sph + v % sph;
+}
+
+// PK: query segment v of the packed head pairs (ceil(G / 2) per group, a last
+// pair of an odd group its head twice): of the pair's first or second head.
+__host__ __device__ __forceinline__ int strm_pair_seg(int v, int second, int sph, int G) {
+  const int Gp = (G + 1) / 2, pair = v / sph, g = 2 * (pair % Gp) + second;
+  return ((pair / Gp) * G + (g < G ? g : G - 1)) * sph + v % sph;
+}
+
 // A wave-uniform value in scalar registers (the loop state that forms it looks
 // divergent to the compiler).
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -133,8 +230,34 @@ __device__ __forceinline__ void wait_barrier() {
   static_assert(N < 64, "vmcnt field");
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
 }
+// The same for a count known at run time (16 at most: more waits for more).
+__device__ __forceinline__ void wait_counted(int n) {
+  switch (n) {
+    case 0: return wait_barrier<0>();
+    case 1: return wait_barrier<1>();
+    case 2: return wait_barrier<2>();
+    case 3: return wait_barrier<3>();
+    case 4: return wait_barrier<4>();
+    case 5: return wait_barrier<5>();
+    case 6: return wait_barrier<6>();
+    case 7: return wait_barrier<7>();
+    case 8: return wait_barrier<8>();
+    case 9: return wait_barrier<9>();
+    case 10: return wait_barrier<10>();
+    case 11: return wait_barrier<11>();
+    case 12: return wait_barrier<12>();
+    case 13: return wait_barrier<13>();
+    case 14: return wait_barrier<14>();
+    case 15: return wait_barrier<15>();
+    default: return wait_barrier<16>();
+  }
+}
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+__device__ __forceinline__ float sum_x32(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
 __device__ __forceinline__ float max_x32(float v) {
   const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
@@ -153,9 +276,10 @@ __device__ __forceinline__ void wait_segment(int rem) {
   else wait_barrier<2 * KI + (SL > 3 ? 2 : 1) * QW>();
 }
 
-template <int QB, int P, int NS, int SL>
+template <typename T, int QB, int P, int NS, int SL, bool HB>
 __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
-  constexpr int QT = (QB + 1) / 2;                    // 32-row query blocks
+  constexpr int QT = HB ? QB : (QB + 1) / 2;          // query blocks
+  constexpr int EL = Tile<HB>::EL, BR = Tile<HB>::ROWS;
   constexpr int KG = kWaves / NS, CAP = 2 * KG;      // wave groups (key windows), tiles per round
   constexpr int QI = NS * P * QB * 2;                 // query DMA instructions per segment
   constexpr int QW = (QI + kWaves - 1) / kWaves;      // of each wave (past QI: an earlier one again)
@@ -236,33 +360,33 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
   source(cur, sc);
   int fo[4];  // this lane's fragment bytes of the four MFMA steps of a segment
 #pragma unroll
-  for (int j = 0; j < 4; ++j) fo[j] = strm_frag(j, l);
+  for (int j = 0; j < 4; ++j) fo[j] = strm_key_frag(HB, j, l);
 
-  f32x16 acc[QT];
-  const int nseg = a.nseg;  // at least SL
-  int slot = 0;             // of the current segment (query buffer and key slot)
-  bool fresh = true;        // nothing in flight for the current round
+  Tile<HB> acc[QT];
+  const int nseg = a.nseg;
+  // with contraction slices the rounds' sums meet in LDS, and rounds of fewer
+  // segments than slots reach past the next round: then each round starts its
+  // pipeline anew
+  const bool serial = NS > 1 || nseg < SL;
+  int slot = 0;       // of the current segment (query buffer and key slot)
+  bool fresh = true;  // nothing in flight for the current round
   while (cur.s < a.n_seq) {
     nxt = cur;
     next_of(nxt);
-    // with contraction slices the rounds' sums meet in LDS, so each round
-    // starts its pipeline anew
-    const bool more = NS == 1 && nxt.s < a.n_seq;
+    const bool more = !serial && nxt.s < a.n_seq;
     if (more) source(nxt, sn);
     if (fresh) {
       slot = 0;
       k_dma(sc, 0, 0);
 #pragma unroll
       for (int i = 0; i + 1 < SL; ++i) {
-        q_dma(sc, i, i);
-        k_dma(sc, i + 1, i + 1);
+        if (i < nseg) q_dma(sc, i, i);
+        if (i + 1 < nseg) k_dma(sc, i + 1, i + 1);
       }
       fresh = false;
     }
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[qt][e] = 0.f;
+    for (int qt = 0; qt < QT; ++qt) acc[qt].clear();
     for (int seg = 0; seg < nseg; ++seg) {
       wait_segment<SL, QW>(more ? SL : nseg - 1 - seg);
       const char* qb = qlds + slot * strm_q_bytes(QB, P, NS) + slice * (P * QB * 16 * kSegBytes);
@@ -277,14 +401,18 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
       if (seg + SL < nseg) k_dma(sc, seg + SL, slot);
       else if (more) k_dma(sn, seg + SL - nseg, slot);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < (HB ? 2 : 4); ++j)
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
           for (int qt = 0; qt < QT; ++qt) {
-            const uint4 qf = *reinterpret_cast<const uint4*>(qb + (p * QB * 16 + qt * 32) * kSegBytes + fo[j]);
-            acc[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qf),
-                                                              __builtin_bit_cast(bf16x8, kf[j]), acc[qt], 0, 0, 0);
+            const uint4 qf = *reinterpret_cast<const uint4*>(qb + (p * QB * 16 + qt * BR) * kSegBytes + fo[j]);
+            if constexpr (HB) {
+              Mma<T>::mac(acc[qt].v[0], qf, kf[j]);
+              Mma<T>::mac(acc[qt].v[1], qf, kf[2 + j]);
+            } else {
+              Mma<T>::mac(acc[qt].v, qf, kf[j]);
+            }
           }
       slot = slot + 1 == SL ? 0 : slot + 1;
     }
@@ -295,14 +423,14 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
       // the slices' sums: slices 1 .. NS-1 publish their accumulators over
       // the (now idle) buffers, slice 0 adds them in slice order
       float* red = reinterpret_cast<float*>(lds);
-      constexpr int W = QT * 16 * 64;  // floats per wave
+      constexpr int W = QT * EL * 64;  // floats per wave
       __syncthreads();
       if (slice > 0) {
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            red[(grp * (NS - 1) + slice - 1) * W + (qt * 16 + e) * 64 + l] = acc[qt][e];
+          for (int e = 0; e < EL; ++e)
+            red[(grp * (NS - 1) + slice - 1) * W + (qt * EL + e) * 64 + l] = acc[qt].get(e);
       }
       __syncthreads();
       if (slice == 0) {
@@ -311,14 +439,18 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
 #pragma unroll
           for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[qt][e] += red[(grp * (NS - 1) + sl - 1) * W + (qt * 16 + e) * 64 + l];
+            for (int e = 0; e < EL; ++e) acc[qt].add(e, red[(grp * (NS - 1) + sl - 1) * W + (qt * EL + e) * 64 + l]);
       }
-      __syncthreads();  // before the next round's DMA overwrites them
+    }
+    if (serial) {
+      __syncthreads();  // before the next round's DMA overwrites what this one's waves read
       fresh = true;
     }
     if (slice == 0) {
       // register e of a block holds query row 8 (e / 4) + 4 (l / 32) + e % 4
-      // (registers 0-7: its first 16 rows), column l % 32 the key
+      // (registers 0-7: its first 16 rows), column l % 32 the key; of a block
+      // of 16 rows, register 4 h + i row 4 (l / 16) + i, column l % 16 of the
+      // keys' half h
       const int key = k0 + (l & 31);
       auto store = [&](int g, float v) __attribute__((always_inline)) {
         if (l >= 32 || key >= k1) return;
@@ -334,13 +466,26 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
       for (int b = 0; b < QB; ++b) {
         if (16 * b >= cur.sd.n_rows) break;
         float v = -INFINITY;
+        if constexpr (HB) {
+          float w = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int ee = 8 * (b & 1) + e;
-          const int row = 32 * (b >> 1) + 8 * (ee >> 2) + 4 * (l >> 5) + (ee & 3);
-          v = fmaxf(v, row < cur.sd.n_rows ? acc[b >> 1][ee] : -INFINITY);
+          for (int e = 0; e < 4; ++e) {
+            const bool ok = 16 * b + 4 * (l >> 4) + e < cur.sd.n_rows;
+            v = fmaxf(v, ok ? acc[b].get(e) : -INFINITY);
+            w = fmaxf(w, ok ? acc[b].get(4 + e) : -INFINITY);
+          }
+          v = max_x32(v), w = max_x32(w);
+          v = fmaxf(v, __shfl_xor(v, 16, 32)), w = fmaxf(w, __shfl_xor(w, 16, 32));
+          v = (l & 16) ? w : v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int ee = 8 * (b & 1) + e;
+            const int row = 32 * (b >> 1) + 8 * (ee >> 2) + 4 * (l >> 5) + (ee & 3);
+            v = fmaxf(v, row < cur.sd.n_rows ? acc[b >> 1].get(ee) : -INFINITY);
+          }
+          v = max_x32(v);
         }
-        v = max_x32(v);
         const int g = a.group_rows ? (cur.sd.q0 + 16 * b) / a.group_rows : 0;
         if (g != gcur) {
           if (gcur >= 0) store(gcur, vg);
@@ -354,7 +499,448 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
     }
     cur = nxt;
     sc = sn;
-    if (NS > 1 && cur.s < a.n_seq) source(cur, sc);
+    if (serial && cur.s < a.n_seq) source(cur, sc);
+  }
+}
+
+// ---- SOFTMAX mode: the two passes over the keys ------------------------------------------
+// The same pipeline with S^T = K Q^T (keys as the A operand): a lane holds one
+// query row and 16 of the wave's 32 keys, so a head's exponentials are summed,
+// or its probabilities accumulated, in registers.  The contraction runs over
+// the query heads in order, sph segments each, and every head is closed in
+// registers.
+// Per score one FMA, one v_exp_f32 and one add: a third of the pass's memory
+// time at 64 rows, hidden behind it.  Whole calls, against passes that held
+// statistics per wave and took the keys to registers in operand shape (bf16
+// rows x keys, query / key heads): 64 x 46080, 28 of 128 191 -> 172 us; 32 x
+// 32768, 28 of 128 115 -> 96; 128 x 50176 374 -> 270; 32 x 2304 92 -> 44; 40 x
+// 65536, 32 / 8 of 128 158 -> 158 (reading the keys again for each query head:
+// 201); 10 x 34788, 32 / 8 of 128 111 -> 88 (heads not paired: 118); fp32, 56 x
+// 11050, 28 of 128 360 -> 162.
+//  pass 1 (PROB = false): the row's sum of exp2(s c2) over the wave's keys
+//   against 0; rows whose sum leaves (2^-64, 2^64) or that see no key are
+//   summed again against their max.  The waves' pairs meet in LDS, where one
+//   wave (in turn) adds them in wave order a segment later to the workgroup's
+//   table of heads and rows, written to memory once at the end: one pair per
+//   row and workgroup.  (A store per head inside the loop is one more
+//   operation that the in-order wait for the next segment's DMA counts, which
+//   then waits for the segment after: 1.3 us a head.  Only where the table
+//   does not fit LDS -- hundreds of heads -- do the pairs go to memory there.)
+//  pass 2 (PROB = true): adds exp2(s c2 - L), L = M log2 e + log2 Z of the row,
+//   over the heads, then the max over the rows (lanes).
+// NS > 1 (few tiles) deals the query heads to NS slices of the waves, as
+// qer_strm_kernel does the contraction; pass 2 adds the slices' sums in order.
+// Grouped heads: KS = 0 reads the key head's segments again for every query
+// head (from L2); KS = 1, 2 or 4 segments per head (one slice) stay in
+// registers for the group's heads, a few slots hold the next ones and the LDS
+// freed takes more query segments.  Query DMA comes every step, key DMA KS
+// steps per group, so the wait for a step's data counts what was issued since
+// from two bit histories.  At most 16 query rows (PK): two heads of a group
+// fill a 32-row block, the pair being the unit that steps, slices and closes.
+template <typename T, int QB, int NS, int SL, bool PROB, int KS, bool PK>
+__global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a) {
+  static_assert(!PK || QB == 1, "two heads share a block of 32 rows");
+  constexpr bool HB = !PK && QB % 2 != 0;  // blocks of 16 rows
+  constexpr int QT = HB ? QB : (QB + 1) / 2, ROWS = 16 * QB, EL = Tile<HB>::EL, BR = Tile<HB>::ROWS;
+  constexpr int QBB = PK ? 2 : QB, PAIRS = 16 * QBB;  // query blocks in LDS; statistics pairs of a step and wave
+  constexpr int KG = kWaves / NS, CAP = 2 * KG;
+  constexpr int QI = NS * QBB * 2, QW = (QI + kWaves - 1) / kWaves;
+  extern __shared__ __align__(16) char lds[];
+  const int tid = threadIdx.x, l = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = wave % NS, grp = wave / NS;
+  char* const qlds = lds;
+  const int slots = KS ? a.slots : SL;
+  char* const klds = lds + slots * strm_q_bytes(QBB, 1, NS) + wave * soft_key_slots(SL, KS) * kKeyBytes;
+  // past the buffers: pass 2's row constants L [H][ROWS]; pass 1's table
+  // [H][ROWS] of the workgroup's pairs, then the waves' pairs [2][8][PAIRS]
+  float* const lsh = reinterpret_cast<float*>(lds + soft_ring(QB, NS, slots, KS, PK));
+  float2* const table = reinterpret_cast<float2*>(lsh);
+  float2* const red = table + (PROB || a.direct ? 0 : a.H * ROWS);
+  const uint32_t q_dst = lds_addr(qlds), k_dst = lds_addr(klds);
+  if (blockIdx.x == 0 && a.clear)
+    for (int i = tid; i < a.nclear; i += kThreads) a.clear[i] = 0;
+  for (int i = tid; i < a.H * ROWS; i += kThreads) {
+    if constexpr (PROB) {
+      const int h = i / ROWS, q = i - h * ROWS;
+      const float2 st = a.stats[(int64_t)h * a.nq_total + a.q0 + (q < a.n_q ? q : a.n_q - 1)];
+      lsh[i] = st.x * 1.44269504088896341f + __log2f(st.y);
+    } else if (!a.direct) {
+      table[i] = make_float2(-INFINITY, 0.f);
+    }
+  }
+  const QerStreamDesc sd{0, a.n_vis, 0, a.tiles, a.q0, a.n_q, 0};
+  const int wg = (int)blockIdx.x;
+  const Piece pc = strm_piece(sd, (int)((int64_t)a.tiles * wg / a.nwg), (int)((int64_t)a.tiles * (wg + 1) / a.nwg), CAP);
+
+  // PK: the lane's head of the pair; the query row of lane l in block qt
+  const int second = PK ? (l >> 4) & 1 : 0;
+  auto row_of = [&](int qt) __attribute__((always_inline)) { return PK ? l & 15 : BR * qt + l % BR; };
+  // keys that this lane's row of block qt sees
+  int lim[QT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    lim[qt] = a.n_vis;
+    if (!PROB && a.soft_nf) {
+      const int q = row_of(qt);
+      const int v = q < a.n_q ? a.soft_offs[a.soft_nf[(a.q0 + q) / a.group_rows]] : 0;
+      lim[qt] = v < 0 ? 0 : (v > a.n_vis ? a.n_vis : v);
+    }
+  }
+  const int nseg = a.nseg, heads = nseg / a.sph;  // of a slice (PK: pairs of heads)
+  const int Gs = PK ? (a.G + 1) / 2 : a.G;       // of those, how many share a key head
+  uint32_t qoff[QW];
+#pragma unroll
+  for (int j = 0; j < QW; ++j)
+    qoff[j] = (uint32_t)strm_q_off(PK ? (wave + kWaves * j) % QI & 1 : (wave + kWaves * j) % QI, l, 1, QB, a.nq_total,
+                                   a.n_q, a.q_row_bytes, (int64_t)nseg * kSegBytes);
+  const uint8_t* const qbase = a.Q + (int64_t)a.q0 * a.q_row_bytes;
+  auto q_dma = [&](int seg, int buf) __attribute__((always_inline)) {
+    const uint8_t* base = uniform(qbase + (int64_t)seg * kSegBytes);
+    const uint32_t dst = uniform(q_dst + buf * strm_q_bytes(QBB, 1, NS));
+#pragma unroll
+    for (int j = 0; j < QW; ++j) {
+      const int i = (wave + kWaves * j) % QI;  // PK: slice, head of the pair, 8 rows
+      if (PK) base = uniform(qbase + (int64_t)strm_pair_seg(i / 4 * nseg + seg, (i >> 1) & 1, a.sph, a.G) * kSegBytes);
+      dma(base, qoff[j], dst + 1024 * i);
+    }
+  };
+  struct Src {
+    const uint8_t* kbase;
+    uint32_t koff[kKeyDma];
+    int k0, k1;
+  };
+  auto source = [&](int r, Src& o) __attribute__((always_inline)) {
+    strm_window(pc, r, grp, KG, a.n_vis, o.k0, o.k1);
+    o.kbase = a.K + (int64_t)(o.k1 > o.k0 ? o.k0 : 0) * a.k_row_bytes;
+#pragma unroll
+    for (int i = 0; i < kKeyDma; ++i)
+      o.koff[i] = (uint32_t)(strm_row(i, l, o.k1 - o.k0) * a.k_row_bytes) + 16u * strm_chunk(i, l);
+  };
+  auto k_dma = [&](const Src& o, int seg, int slot) __attribute__((always_inline)) {
+    const int ks = KS ? seg : strm_key_seg(slice * nseg + seg, a.sph, Gs);
+    const uint8_t* base = uniform(o.kbase + (int64_t)ks * kSegBytes);
+    const uint32_t dst = uniform(k_dst + slot * kKeyBytes);
+#pragma unroll
+    for (int i = 0; i < kKeyDma; ++i) dma_nt(base, o.koff[i], dst + 1024 * i);
+  };
+
+  Src sc, sn;
+  source(0, sc);
+  int fo[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) fo[j] = strm_key_frag(HB, j, l);
+  // (the loads above are done before the first DMA: the waits below count
+  // later operations only)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // slices, and rounds of fewer segments than slots, start their pipeline
+  // anew every round
+  constexpr int KEYS = soft_key_slots(SL, KS);
+  const int nkey = KS * (heads / Gs);  // KS: key segments
+  const bool serial = KS ? nkey < KEYS : NS > 1 || nseg < SL;
+  // KS: bit i of the histories: step - 1 - i brought a query (key) segment
+  uint32_t qhist = 0, khist = 0;
+  auto low = [](int n) __attribute__((always_inline)) { return n < 32 ? (1u << n) - 1 : ~0u; };
+  auto start = [&]() __attribute__((always_inline)) {
+    k_dma(sc, 0, 0);
+    if constexpr (KS > 0) {
+#pragma unroll
+      for (int i = 1; i < KEYS; ++i)
+        if (i < nkey) k_dma(sc, i, i);
+      for (int i = 0; i + 1 < slots; ++i) q_dma(i, i);  // (the plan has slots <= nseg)
+      qhist = low(slots - 1);
+      khist = 0;
+    } else {
+#pragma unroll
+      for (int i = 0; i + 1 < SL; ++i) {
+        if (i < nseg) q_dma(i, i);
+        if (i + 1 < nseg) k_dma(sc, i + 1, i + 1);
+      }
+    }
+  };
+  start();
+  Tile<HB> acc[QT], prob[QT];
+  // sum and max over the lanes that share a query row
+  auto row_sum = [&](float v) __attribute__((always_inline)) {
+    v = sum_x32(v);
+    return HB ? v + __shfl_xor(v, 16, 32) : v;
+  };
+  auto row_max = [&](float v) __attribute__((always_inline)) {
+    v = max_x32(v);
+    return HB ? fmaxf(v, __shfl_xor(v, 16, 32)) : v;
+  };
+  auto multiply = [&](const uint4 (&kf)[4], const char* qb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < (HB ? 2 : 4); ++j)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const uint4 qf = *reinterpret_cast<const uint4*>(qb + qt * BR * kSegBytes + fo[j]);
+        if constexpr (HB) {
+          Mma<T>::mac(acc[qt].v[0], kf[j], qf);
+          Mma<T>::mac(acc[qt].v[1], kf[2 + j], qf);
+        } else {
+          Mma<T>::mac(acc[qt].v, kf[j], qf);
+        }
+      }
+  };
+  int slot = 0, kslot = 0;
+  // pass 1: the slice's head whose pairs wait in LDS, their round, and the half they wait in
+  int pend = -1, pend_round = 0, par = 0;
+  // query head of the slice's unit u (PK: its first or second; -1: an odd group has none)
+  auto head_of = [&](int u, int sec) __attribute__((always_inline)) {
+    u += slice * heads;
+    if (!PK) return u;
+    const int g = 2 * (u % Gs) + sec;
+    return g < a.G ? (u / Gs) * a.G + g : -1;
+  };
+  auto add_pairs = [&]() __attribute__((always_inline)) {
+    if (!PROB && pend >= 0) {
+      if (grp == pend % KG) {
+        const float2* p = red + (par ^ 1) * kWaves * PAIRS + slice * PAIRS;
+        for (int i = l; i < PAIRS; i += 64) {
+          const int h = head_of(pend, PK && i >= 16), q = PK ? i & 15 : i;
+          if (h < 0) continue;
+          const int64_t row = (int64_t)h * a.nq_total + a.q0 + q;
+          float2* const mem = a.stats_part + ((row >> 4) * a.nparts + wg) * 16 + (row & 15);
+          float2 t = make_float2(-INFINITY, 0.f);  // of the rounds before
+          if (!a.direct) t = table[h * ROWS + q];
+          else if (pend_round > 0 && q < a.n_q) t = *mem;
+          float2 v[KG];
+#pragma unroll
+          for (int w = 0; w < KG; ++w) v[w] = p[w * NS * PAIRS + i];
+          float M = t.y > 0.f ? t.x : -INFINITY;
+          bool zero = !(t.y > 0.f) || t.x == 0.f;  // every pair that counts is against 0
+#pragma unroll
+          for (int w = 0; w < KG; ++w)
+            if (v[w].y > 0.f) {
+              M = fmaxf(M, v[w].x);
+              zero = zero && v[w].x == 0.f;
+            }
+          float Z = t.y > 0.f ? (zero ? t.y : t.y * __expf(t.x - M)) : 0.f;
+#pragma unroll
+          for (int w = 0; w < KG; ++w)
+            if (v[w].y > 0.f) Z += zero ? v[w].y : v[w].y * __expf(v[w].x - M);
+          if (!a.direct) table[h * ROWS + q] = make_float2(M, Z);
+          else if (q < a.n_q) *mem = make_float2(M, Z);
+        }
+      }
+      pend = -1;
+    }
+  };
+  for (int r = 0; r < pc.rounds; ++r) {
+    const bool more = !serial && r + 1 < pc.rounds;
+    if (r + 1 < pc.rounds) source(r + 1, sn);
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) acc[qt].clear(), prob[qt].clear();
+    uint32_t full = 0;  // bit qt: every lane's row of the block sees all 32 keys
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt)
+      if (__builtin_amdgcn_ballot_w64((lim[qt] < sc.k1 ? lim[qt] : sc.k1) - sc.k0 < 32) == 0) full |= 1u << qt;
+    auto close = [&](int unit) __attribute__((always_inline)) {
+      // the slice's query head (pair) `unit` is complete (PK: lane l holds its
+      // head l / 16 % 2)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        if constexpr (PROB) {
+          const int h = head_of(unit, second);
+          const float L = h < 0 ? INFINITY : lsh[h * ROWS + row_of(qt)];
+#pragma unroll
+          for (int e = 0; e < EL; ++e) prob[qt].add(e, __builtin_amdgcn_exp2f(fmaf(acc[qt].get(e), a.c2, -L)));
+        } else {
+          const int n = (lim[qt] < sc.k1 ? lim[qt] : sc.k1) - sc.k0 - Tile<HB>::first(l);  // keys seen, from this lane's first
+          float z = 0.f, mx = 0.f;
+          if (sc.k1 > sc.k0) {  // (a wave without keys leaves an empty pair)
+            if ((full >> qt) & 1u) {
+#pragma unroll
+              for (int e = 0; e < EL; ++e) z += __builtin_amdgcn_exp2f(acc[qt].get(e) * a.c2);
+            } else {
+#pragma unroll
+              for (int e = 0; e < EL; ++e) {
+                const float x = __builtin_amdgcn_exp2f(acc[qt].get(e) * a.c2);
+                z += Tile<HB>::key(e) < n ? x : 0.f;
+              }
+            }
+            z = row_sum(z);
+            if (!(z < 0x1p64f && z > 0x1p-64f)) {
+              mx = -INFINITY;
+#pragma unroll
+              for (int e = 0; e < EL; ++e)
+                if (Tile<HB>::key(e) < n) mx = fmaxf(mx, acc[qt].get(e));
+              mx = row_max(mx);
+              const float mc = mx * a.c2;
+              z = 0.f;
+#pragma unroll
+              for (int e = 0; e < EL; ++e)
+                if (Tile<HB>::key(e) < n) z += __builtin_amdgcn_exp2f(fmaf(acc[qt].get(e), a.c2, -mc));
+              z = row_sum(z);
+            }
+          }
+          if (l < BR) red[(par * kWaves + wave) * PAIRS + BR * qt + l] = make_float2(mx * a.soft_scale, z);
+        }
+        acc[qt].clear();
+      }
+      if constexpr (!PROB) {
+        pend = unit;
+        pend_round = r;
+        par ^= 1;
+      }
+    };
+    if constexpr (KS > 0) {
+      int t = 0, ks = 0;
+      for (int kh = 0; kh < heads / Gs; ++kh) {
+        uint4 kf[KS][4];
+        for (int g = 0; g < Gs; ++g) {
+#pragma unroll
+          for (int i = 0; i < KS; ++i) {
+            // query segment t came slots - 1 steps ago (before that step's
+            // keys), these keys KEYS Gs steps ago: KEYS slots of KS segments a group
+            int n = QW * __builtin_popcount(qhist & low(slots - 2)) + kKeyDma * __builtin_popcount(khist & low(slots - 1));
+            if (g == 0) {
+              const uint32_t m = low(KEYS * Gs - 1);
+              n = min(n, QW * __builtin_popcount(qhist & m) + kKeyDma * __builtin_popcount(khist & m));
+            }
+            wait_counted((int)uniform((uint32_t)n));
+            const char* qb = qlds + slot * strm_q_bytes(QBB, 1, NS);
+            const int before = slot == 0 ? slots - 1 : slot - 1;
+            const bool q_more = t + slots - 1 < nseg || more;
+            if (q_more) q_dma(t + slots - 1 < nseg ? t + slots - 1 : t + slots - 1 - nseg, before);
+            qhist = 2 * qhist + q_more;
+            khist = 2 * khist;
+            if (g == 0) {
+              const char* kb = klds + kslot * kKeyBytes;
+#pragma unroll
+              for (int j = 0; j < 4; ++j) kf[i][j] = *reinterpret_cast<const uint4*>(kb + fo[j]);
+              wait_lds();
+              if (ks + KEYS < nkey) k_dma(sc, ks + KEYS, kslot);
+              else if (more) k_dma(sn, ks + KEYS - nkey, kslot);
+              khist += ks + KEYS < nkey || more;
+              ++ks;
+              kslot = kslot + 1 == KEYS ? 0 : kslot + 1;
+            }
+            multiply(kf[i], qb);
+            add_pairs();
+            slot = slot + 1 == slots ? 0 : slot + 1;
+            ++t;
+          }
+          close(kh * Gs + g);
+        }
+      }
+    }
+    int unit = 0, hs = 0;
+    for (int seg = 0; KS == 0 && seg < nseg; ++seg) {
+      wait_segment<SL, QW>(more ? SL : nseg - 1 - seg);
+      const char* qb = qlds + slot * strm_q_bytes(QBB, 1, NS) + slice * (QBB * 16 * kSegBytes);
+      const char* kb = klds + slot * kKeyBytes;
+      const int before = slot == 0 ? SL - 1 : slot - 1;
+      if (seg + SL - 1 < nseg) q_dma(seg + SL - 1, before);
+      else if (more) q_dma(seg + SL - 1 - nseg, before);
+      uint4 kf[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kf[j] = *reinterpret_cast<const uint4*>(kb + fo[j]);
+      wait_lds();
+      if (seg + SL < nseg) k_dma(sc, seg + SL, slot);
+      else if (more) k_dma(sn, seg + SL - nseg, slot);
+      multiply(kf, qb);
+      add_pairs();
+      if (++hs == a.sph) {
+        hs = 0;
+        close(unit++);
+      }
+      slot = slot + 1 == SL ? 0 : slot + 1;
+    }
+    if constexpr (PROB && PK)  // the pair's heads
+#pragma unroll
+      for (int e = 0; e < EL; ++e) prob[0].add(e, __shfl_xor(prob[0].get(e), 16, 32));
+    if constexpr (PROB && NS > 1) {
+      // the slices' sums over the (now idle) buffers, added in slice order
+      float* sum = reinterpret_cast<float*>(lds);
+      constexpr int W = QT * EL * 64;
+      __syncthreads();
+      if (slice > 0) {
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+          for (int e = 0; e < EL; ++e) sum[(grp * (NS - 1) + slice - 1) * W + (qt * EL + e) * 64 + l] = prob[qt].get(e);
+      }
+      __syncthreads();
+      if (slice == 0) {
+#pragma unroll
+        for (int sl = 1; sl < NS; ++sl)
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+            for (int e = 0; e < EL; ++e) prob[qt].add(e, sum[(grp * (NS - 1) + sl - 1) * W + (qt * EL + e) * 64 + l]);
+      }
+    }
+    if (PROB && slice == 0) {
+      // m = max over the rows of each query of the head sum: over the lanes of
+      // a block, then over the query's blocks; of the BR lanes that share
+      // their keys, lane e (< EL) ends with the key of element e
+      const int e = l % EL, key = sc.k0 + Tile<HB>::key(e) + Tile<HB>::first(l);
+      auto store = [&](int g, const float (&v)[EL]) __attribute__((always_inline)) {
+        // (a bit-mask blend: a select chain would become an indexed scratch load)
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 0; i < EL; ++i) bits |= __float_as_uint(v[i]) & (e == i ? ~0u : 0u);
+        if (l % BR >= EL || key >= sc.k1) return;
+        const float x = __uint_as_float(bits) * a.inv_h;
+        float* dst = a.m + g * a.m_stride + key;
+        const bool cont = a.group_rows ? (int64_t)g * a.group_rows < a.q0 : a.accumulate != 0;
+        *dst = cont ? fmaxf(*dst, x) : x;
+      };
+      float vg[EL];
+      if (!a.group_rows) {  // one query: the lane's rows first
+#pragma unroll
+        for (int i = 0; i < EL; ++i) {
+          float v = -INFINITY;
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) v = fmaxf(v, BR * qt + l % BR < a.n_q ? prob[qt].get(i) : -INFINITY);
+#pragma unroll
+          for (int o = BR / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 32));
+          vg[i] = v;
+        }
+        store(0, vg);
+      }
+      int gcur = -1;
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        if (!a.group_rows || 16 * b >= a.n_q) break;
+        const int g = (a.q0 + 16 * b) / a.group_rows;
+        if (g != gcur) {
+          if (gcur >= 0) store(gcur, vg);
+          gcur = g;
+#pragma unroll
+          for (int i = 0; i < EL; ++i) vg[i] = -INFINITY;
+        }
+        constexpr int SH = HB ? 0 : 1;  // blocks of 16 rows per tile: 2^SH
+        const bool mine = (HB || ((l >> 4) & 1) == (b & 1)) && 16 * (b & ~SH) + l % BR < a.n_q;
+#pragma unroll
+        for (int i = 0; i < EL; ++i) {
+          float v = mine ? prob[b >> SH].get(i) : -INFINITY;
+#pragma unroll
+          for (int o = BR / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 32));
+          vg[i] = fmaxf(vg[i], v);
+        }
+      }
+      if (gcur >= 0) store(gcur, vg);
+    }
+    sc = sn;
+    if (serial && r + 1 < pc.rounds) {
+      __syncthreads();  // before the next round's DMA overwrites what this one's waves read
+      add_pairs();
+      slot = kslot = 0;
+      start();
+    }
+  }
+  if constexpr (!PROB) {
+    __syncthreads();
+    add_pairs();
+    __syncthreads();
+    for (int i = tid; i < (a.direct ? 0 : a.H * ROWS); i += kThreads) {
+      const int h = i / ROWS, q = i - h * ROWS;
+      const int64_t row = (int64_t)h * a.nq_total + a.q0 + q;
+      if (q < a.n_q) a.stats_part[((row >> 4) * a.nparts + wg) * 16 + (row & 15)] = table[i];
+    }
   }
 }
 
@@ -372,23 +958,28 @@ constexpr int strm_slots(int QB, int P, int NS) {
 // Address model of qer_strm_kernel (dry run): the rounds of every workgroup
 // as the kernel walks them, its key and query DMA at both ends of each
 // round's segments, the LDS it fills and reads, its stores of m.
-void model_strm(const StrmArgs& a, int QB, int P, int NS, int SL, size_t lds) {
-  const int KG = kWaves / NS, CAP = 2 * KG, QI = NS * P * QB * 2, KI = kKeyDma, QT = (QB + 1) / 2;
+void model_strm(const StrmArgs& a, int QB, int P, int NS, int SL, bool HB, size_t lds) {
+  const int KG = kWaves / NS, CAP = 2 * KG, QI = NS * P * QB * 2, KI = kKeyDma, QT = HB ? QB : (QB + 1) / 2;
+  const int BR = HB ? 16 : 32, EL = HB ? 8 : 16;
   const int64_t slice_bytes = (int64_t)a.nseg * kSegBytes;
   dry_range((int64_t)lds, 0, kLdsMax + 1, "score: LDS beyond a CU's 160 KiB");
-  dry_range(a.nseg, SL, INT32_MAX, "score: fewer segments than slots");
+  dry_range(a.nseg, 1, INT32_MAX, "score: segments");
   dry_range(a.row_bytes - NS * slice_bytes, 0, 1, "score: the slices' segments are not the row");
   if (a.xcd_order) dry_range(a.nwg % 8, 0, 1, "score: XCD order needs whole groups of 8 workgroups");
   if (a.clear && a.nclear > 0) dry_access(a.clear, 0, 4 * (int64_t)a.nclear, "score: arrival counters");
   const int64_t ring = SL * (int64_t)(strm_q_bytes(QB, P, NS) + kWaves * kKeyBytes);
   dry_lds(0, ring, (int64_t)lds, "score: buffers");
-  if (NS > 1) dry_lds(0, (int64_t)KG * (NS - 1) * QT * 16 * 256, (int64_t)lds, "score: slice sums");
+  if (NS > 1) dry_lds(0, (int64_t)KG * (NS - 1) * QT * EL * 256, (int64_t)lds, "score: slice sums");
   int frag = 0;  // the last byte a fragment read reaches in its 32 rows
   for (int j = 0; j < 4; ++j)
-    for (int l = 0; l < 64; ++l) frag = std::max(frag, strm_frag(j, l) + 16);
+    for (int l = 0; l < 64; ++l) frag = std::max(frag, strm_key_frag(HB, j, l) + 16);
   dry_range(frag, 0, 32 * kSegBytes + 1, "score: fragment past its 32 rows");
+  dry_lds((SL - 1) * (int64_t)(kWaves * kKeyBytes) + SL * (int64_t)strm_q_bytes(QB, P, NS) + (kWaves - 1) * kKeyBytes, frag,
+          (int64_t)lds, "score: key fragment");
+  if (HB)
+    for (int l = 0; l < 64; ++l) frag = l ? std::max(frag, strm_frag16(1, l) + 16) : 16;
   dry_lds((SL - 1) * (int64_t)strm_q_bytes(QB, P, NS) + (NS - 1) * P * QB * 16 * kSegBytes +
-              ((P - 1) * QB * 16 + (QT - 1) * 32) * kSegBytes, frag, (int64_t)lds, "score: query fragment");
+              ((P - 1) * QB * 16 + (QT - 1) * BR) * kSegBytes, frag, (int64_t)lds, "score: query fragment");
   const QerStreamDesc* seq = nullptr;
   if (a.seq) {
     seq = static_cast<const QerStreamDesc*>(dry_shadow(a.seq));
@@ -443,86 +1034,320 @@ void model_strm(const StrmArgs& a, int QB, int P, int NS, int SL, size_t lds) {
   }
 }
 
-template <int QB, int P, int NS, int SL>
+// LDS of a SOFTMAX pass past the buffers
+constexpr int64_t soft_more(int QB, bool PK, int64_t H, bool prob, bool direct) {
+  return prob ? 4 * H * 16 * QB : 8 * ((direct ? 0 : H * QB) + 2 * kWaves * (PK ? 2 : QB)) * 16;
+}
+
+// Address model of qer_strm_soft_kernel (dry run)
+void model_strm_soft(const StrmSoftArgs& a, int QB, int NS, int SL, int KS, bool PK, bool prob, size_t lds) {
+  const int ROWS = 16 * QB, KG = kWaves / NS, CAP = 2 * KG, QT = !PK && QB % 2 ? QB : (QB + 1) / 2, QBB = PK ? 2 : QB;
+  const bool HB = !PK && QB % 2;
+  const int BR = HB ? 16 : 32, EL = HB ? 8 : 16;
+  const int Gs = PK ? (a.G + 1) / 2 : a.G, units = a.H / a.G * Gs;
+  const int64_t slice_bytes = (int64_t)a.nseg * kSegBytes;
+  dry_range((int64_t)lds, 0, kLdsMax + 1, "score: LDS beyond a CU's 160 KiB");
+  dry_range(a.nseg, 1, INT32_MAX, "score: segments");
+  dry_range(a.q_row_bytes - (int64_t)a.H * a.sph * kSegBytes, 0, 1, "score: the segments are not the query row");
+  dry_range(a.H % a.G, 0, 1, "score: whole groups");
+  dry_range(units % NS, 0, 1, "score: whole heads per slice");
+  dry_range(a.n_q, 1, (int64_t)ROWS + 1, "score: query rows of a chunk");
+  dry_range(NS * a.nseg - units * a.sph, 0, 1, "score: the heads are not the segments");
+  if (a.clear && a.nclear > 0) dry_access(a.clear, 0, 4 * (int64_t)a.nclear, "score: arrival counters");
+  const int64_t ring = soft_ring(QB, NS, SL, KS, PK);
+  if (KS) {
+    dry_range(a.slots, 2, a.nseg + 1, "score: query slots");
+    dry_range(a.sph - KS, 0, 1, "score: segments of a head");
+    dry_range(a.k_row_bytes - (int64_t)KS * (a.H / a.G) * kSegBytes, 0, 1, "score: the key heads are not the row");
+  }
+  dry_lds(0, ring + soft_more(QB, PK, a.H, prob, a.direct), (int64_t)lds, "score: buffers");
+  if (prob && NS > 1) dry_lds(0, (int64_t)KG * (NS - 1) * QT * EL * 256, ring, "score: slice sums");
+  int frag = 0;
+  for (int j = 0; j < 4; ++j)
+    for (int l = 0; l < 64; ++l) frag = std::max(frag, strm_key_frag(HB, j, l) + 16);
+  dry_lds(SL * (int64_t)strm_q_bytes(QBB, 1, NS) + (kWaves * soft_key_slots(SL, KS) - 1) * (int64_t)kKeyBytes, frag, ring,
+          "score: key fragment");
+  if (HB)
+    for (int l = 0; l < 64; ++l) frag = l ? std::max(frag, strm_frag16(1, l) + 16) : 16;
+  dry_lds((SL - 1) * (int64_t)strm_q_bytes(QBB, 1, NS) + (NS - 1) * QBB * 16 * kSegBytes + (QT - 1) * BR * kSegBytes, frag,
+          (int64_t)lds, "score: query fragment");
+  if (prob)
+    for (int64_t i : {(int64_t)a.q0, (int64_t)(a.H - 1) * a.nq_total + a.q0 + a.n_q - 1})
+      dry_access(a.stats, 8 * i, 8, "score: pass-2 statistics");
+  if (!prob && a.soft_nf) {
+    const int32_t* nf_h = static_cast<const int32_t*>(dry_shadow(a.soft_nf));
+    if (!nf_h) dry_range(0, 0, 0, "score: per-query frame counts without a host copy");
+    for (int q = 0; nf_h && q < a.n_q; ++q) {
+      const int g = (a.q0 + q) / a.group_rows;
+      dry_access(a.soft_nf, 4 * (int64_t)g, 4, "score: per-query frame count");
+      dry_access(a.soft_offs, 4 * (int64_t)nf_h[g], 4, "score: the query's key limit");
+    }
+  }
+  int ks = 0;
+  for (int v = 0; v < NS * a.nseg; ++v) {
+    dry_range(strm_key_seg(v, a.sph, Gs), 0, a.k_row_bytes / kSegBytes, "score: key segment past the row");
+    ks = std::max(ks, strm_key_seg(v, a.sph, Gs));
+    for (int second = 0; PK && second < 2; ++second)
+      dry_range(strm_pair_seg(v, second, a.sph, a.G), 0, a.H * a.sph, "score: query segment past the row");
+  }
+  for (int i = 0; i < 2 * NS * QBB; ++i)
+    for (int l = 0; l < 64; ++l) {
+      const int64_t off = strm_q_off(PK ? i & 1 : i, l, 1, QB, a.nq_total, a.n_q, a.q_row_bytes, slice_bytes);
+      dry_range(off, 0, int64_t(1) << 32, "score: query offset past 32 bits");
+      for (int64_t seg : {int64_t(0), (int64_t)a.nseg - 1}) {
+        const int64_t from = PK ? strm_pair_seg(i / 4 * a.nseg + (int)seg, (i >> 1) & 1, a.sph, a.G) : seg;
+        dry_access(a.Q, a.q0 * a.q_row_bytes + off + from * kSegBytes, 16, "score: query load");
+      }
+    }
+  const QerStreamDesc sd{0, a.n_vis, 0, a.tiles, a.q0, a.n_q, 0};
+  int next = 0;
+  for (int wg = 0; wg < a.nwg; ++wg) {
+    const Piece pc = strm_piece(sd, (int)((int64_t)a.tiles * wg / a.nwg), (int)((int64_t)a.tiles * (wg + 1) / a.nwg), CAP);
+    for (int r = 0; r < pc.rounds; ++r) {
+      for (int w = 0; w < KG; ++w) {
+        int k0, k1;
+        strm_window(pc, r, w, KG, a.n_vis, k0, k1);
+        dry_range(k0 - next, 0, 1, "score: a window begins where the one before ends");
+        dry_range(k1 - k0, 0, 33, "score: window wider than the wave's keys");
+        next = k1 > k0 ? (k1 + 15) / 16 * 16 : next;
+        const int64_t base = (int64_t)(k1 > k0 ? k0 : 0) * a.k_row_bytes;
+        for (int i = 0; i < kKeyDma; ++i)
+          for (int l = 0; l < 64; ++l) {
+            const int64_t off = strm_row(i, l, k1 - k0) * a.k_row_bytes + 16 * strm_chunk(i, l);
+            dry_range(off, 0, int64_t(1) << 32, "score: key offset past 32 bits");
+            dry_access(a.K, base + off, 16, "score: key load");
+            dry_access(a.K, base + off + (int64_t)ks * kSegBytes, 16, "score: key load");
+          }
+        if (prob && k1 > k0) {
+          dry_range(k1 - 1, 0, a.m_stride, "score: key past the row of m");
+          for (int b = 0; b < QB && 16 * b < a.n_q; ++b) {
+            const int64_t q = a.group_rows ? (a.q0 + 16 * b) / a.group_rows : 0;
+            dry_access(a.m, (q * a.m_stride + k0) * 4, 4 * (int64_t)(k1 - k0), "score: m");
+          }
+        }
+      }
+    }
+    if (!prob)
+      for (int64_t row : {(int64_t)a.q0, (int64_t)(a.H - 1) * a.nq_total + a.q0 + a.n_q - 1})
+        dry_access(a.stats_part, (((row >> 4) * a.nparts + wg) * 16 + (row & 15)) * 8, 8, "score: pass-1 statistics");
+  }
+  dry_range(next - 16 * a.tiles, 0, 1, "score: the windows cover the keys");
+}
+
+template <typename T, int QB, int P, int NS, int SL, bool HB>
 int launch_t(const StrmArgs& a, hipStream_t s) {
   constexpr int QT = (QB + 1) / 2;
   constexpr size_t lds = std::max(strm_lds(QB, P, NS, SL), (kWaves / NS) * (NS - 1) * QT * 16 * 256);
   static_assert(lds <= (size_t)kLdsMax, "LDS of a CU");
-  const auto k = qer_strm_kernel<QB, P, NS, SL>;
+  const auto k = qer_strm_kernel<T, QB, P, NS, SL, HB>;
   int rc = allow_lds(k, lds);
   if (rc) return rc;
   if (dry_run()) {
-    model_strm(a, QB, P, NS, SL, lds);
+    model_strm(a, QB, P, NS, SL, HB, lds);
     return COFIE_OK;
   }
   return launch("qer_score", k, dim3((unsigned)a.nwg), dim3(kThreads), lds, s, a);
 }
 
-template <int QB, int P, int NS>
+template <typename T, int QB, int P, int NS, bool HB = false>
 int launch_qb(const StrmArgs& a, hipStream_t s) {
   constexpr int SL = strm_slots(QB, P, NS);
   if constexpr (SL > 2)
-    if (a.nseg >= SL) return launch_t<QB, P, NS, SL>(a, s);
-  return launch_t<QB, P, NS, 2>(a, s);
+    if (a.nseg >= SL) return launch_t<T, QB, P, NS, SL, HB>(a, s);
+  return launch_t<T, QB, P, NS, 2, HB>(a, s);
+}
+
+template <typename T, bool HB>
+int launch_one_term(const StrmArgs& a, int NS, int qb, hipStream_t s) {
+  switch (NS) {
+    case 8: return qb == 1 ? launch_qb<T, 1, 1, 8, HB>(a, s) : launch_qb<T, 2, 1, 8, HB>(a, s);
+    case 4:
+      if (qb == 1) return launch_qb<T, 1, 1, 4, HB>(a, s);
+      if (qb == 2) return launch_qb<T, 2, 1, 4, HB>(a, s);
+      return qb == 3 ? launch_qb<T, 3, 1, 4, HB>(a, s) : launch_qb<T, 4, 1, 4, HB>(a, s);
+    case 2:
+      if (qb == 1) return launch_qb<T, 1, 1, 2, HB>(a, s);
+      if (qb == 2) return launch_qb<T, 2, 1, 2, HB>(a, s);
+      if (qb == 3) return launch_qb<T, 3, 1, 2, HB>(a, s);
+      if constexpr (!HB)
+        if (qb > 4) return launch_qb<T, 8, 1, 2, HB>(a, s);
+      return launch_qb<T, 4, 1, 2, HB>(a, s);
+    default:
+      if (qb == 1) return launch_qb<T, 1, 1, 1, HB>(a, s);
+      if (qb == 2) return launch_qb<T, 2, 1, 1, HB>(a, s);
+      if (qb == 3) return launch_qb<T, 3, 1, 1, HB>(a, s);
+      if constexpr (!HB)
+        if (qb > 4) return launch_qb<T, 8, 1, 1, HB>(a, s);
+      return launch_qb<T, 4, 1, 1, HB>(a, s);
+  }
+}
+
+// Whether ns slices can take whole pairs of heads.
+bool soft_packs(int H, int G, int ns) { return G > 1 && H / G * ((G + 1) / 2) % ns == 0; }
+
+template <typename T, int QB, int NS, int SL, bool PROB, int KS, bool PK>
+int launch_soft_t(const StrmSoftArgs& a, size_t lds, hipStream_t s) {
+  if constexpr (soft_ring(QB, NS, SL, KS, PK) > kLdsMax) {
+    return set_error(COFIE_EHIP, "SOFTMAX streaming plan of %zu bytes", lds);
+  } else {
+    const auto k = qer_strm_soft_kernel<T, QB, NS, SL, PROB, KS, PK>;
+    int rc = allow_lds(k, lds);
+    if (rc) return rc;
+    if (dry_run()) {
+      model_strm_soft(a, QB, NS, KS ? a.slots : SL, KS, PK, PROB, lds);
+      return COFIE_OK;
+    }
+    return launch(PROB ? "qer_soft_score" : "qer_soft_stats", k, dim3((unsigned)a.nwg), dim3(kThreads), lds, s, a);
+  }
+}
+
+// Segment slots: as many segments in flight as LDS holds beside the pass's
+// tables (0: not even two), at most 4, of the queries alone (KS) 6.
+int soft_slots(int QB, int NS, int KS, bool PK, int64_t H, bool prob, bool direct, int nseg) {
+  int sl = KS ? 6 : 4;
+  while (sl > 1 && soft_ring(QB, NS, sl, KS, PK) + soft_more(QB, PK, H, prob, direct) > kLdsMax) --sl;
+  while (sl > 2 && nseg < sl) --sl;
+  return sl < 2 || (KS && nseg < sl) ? 0 : sl;
+}
+
+template <typename T, int QB, int NS, bool PROB, int KS, bool PK>
+int launch_soft_sl(StrmSoftArgs a, hipStream_t s) {
+  a.nseg = a.H / a.G * (PK ? (a.G + 1) / 2 : a.G) * a.sph / NS;
+  a.direct = !PROB && soft_slots(QB, NS, KS, PK, a.H, PROB, false, a.nseg) == 0;
+  a.slots = soft_slots(QB, NS, KS, PK, a.H, PROB, a.direct, a.nseg);
+  if (a.slots == 0) return set_error(COFIE_EHIP, "SOFTMAX streaming plan of %d heads", a.H);
+  const size_t lds = (size_t)(soft_ring(QB, NS, a.slots, KS, PK) + soft_more(QB, PK, a.H, PROB, a.direct));
+  if constexpr (KS > 0) {
+    return launch_soft_t<T, QB, NS, 0, PROB, KS, PK>(a, lds, s);
+  } else {
+    if (a.slots == 4) return launch_soft_t<T, QB, NS, 4, PROB, 0, PK>(a, lds, s);
+    if (a.slots == 3) return launch_soft_t<T, QB, NS, 3, PROB, 0, PK>(a, lds, s);
+    return launch_soft_t<T, QB, NS, 2, PROB, 0, PK>(a, lds, s);
+  }
+}
+
+template <typename T, int QB, int NS, int KS, bool PK>
+int launch_soft_pass(const StrmSoftArgs& a, bool prob, hipStream_t s) {
+  return prob ? launch_soft_sl<T, QB, NS, true, KS, PK>(a, s) : launch_soft_sl<T, QB, NS, false, KS, PK>(a, s);
+}
+
+// Whether a pass can hold KS key segments per group (more than one step each)
+// with its table in LDS.
+bool soft_holds(int QB, int KS, bool PK, const StrmSoftArgs& a, bool prob) {
+  const int Gs = PK ? (a.G + 1) / 2 : a.G;
+  return Gs > 1 && a.sph == KS && soft_slots(QB, 1, KS, PK, a.H, prob, false, a.H / a.G * Gs * a.sph) > 0;
+}
+
+template <typename T, int QB, bool PK>
+int launch_soft_qb(const StrmSoftArgs& a, int ns, bool prob, hipStream_t s) {
+  if constexpr (QB <= 4) {
+    if (ns == 4) return launch_soft_pass<T, QB, 4, 0, PK>(a, prob, s);
+    if (ns == 2) return launch_soft_pass<T, QB, 2, 0, PK>(a, prob, s);
+    if (soft_holds(QB, 4, PK, a, prob)) return launch_soft_pass<T, QB, 1, 4, PK>(a, prob, s);
+  }
+  if (soft_holds(QB, 1, PK, a, prob)) return launch_soft_pass<T, QB, 1, 1, PK>(a, prob, s);
+  if (soft_holds(QB, 2, PK, a, prob)) return launch_soft_pass<T, QB, 1, 2, PK>(a, prob, s);
+  return launch_soft_pass<T, QB, 1, 0, PK>(a, prob, s);
+}
+
+template <typename T>
+int launch_soft(const StrmSoftArgs& a, int ns, bool prob, hipStream_t s) {
+  const int qb = (a.n_q + 15) / 16;
+  if (qb == 1) {
+    if (soft_packs(a.H, a.G, ns)) return launch_soft_qb<T, 1, true>(a, ns, prob, s);
+    return launch_soft_qb<T, 1, false>(a, ns, prob, s);
+  }
+  if (qb == 2) return launch_soft_qb<T, 2, false>(a, ns, prob, s);
+  if (qb == 3) return launch_soft_qb<T, 3, false>(a, ns, prob, s);
+  return qb == 4 ? launch_soft_qb<T, 4, false>(a, ns, prob, s) : launch_soft_qb<T, 8, false>(a, ns, prob, s);
 }
 
 }  // namespace
 
-// The slices: the least time is one round with every wave at work, so tiles
-// that would not give each of a CU's 8 waves 32 keys split the contraction
-// (16 / NS tiles per CU and round).  A slice needs two segments for the
-// pipeline.  Three query terms take at most two slices: their query buffers
-// fill the LDS.  Score kernel, 28 heads of 128: 16 x 144 keys 9.3 us (8
-// slices), 50 x 144 13.9 (8), 128 x 256 37.5 (2); the register-fed kernel with
-// its 4, 4 and 1 slices 16.5, 19.6 and 41.6.
-StrmPlan plan_strm(int64_t tiles, int64_t Lc, int P, int rows, int cus) {
-  StrmPlan p{0, 0, 0};
-  if (tiles <= 0 || Lc % 64 != 0 || Lc / 64 < 2) return p;
-  const int64_t nseg = Lc / 64, per_cu = (tiles + cus - 1) / cus;
-  auto max_rows = [&](int ns) { return P == 3 ? 64 : (ns == 8 ? 32 : (ns == 4 ? 64 : 128)); };
+// Head slices as plan_strm's contraction slices: tiles that give not every
+// wave 32 keys in one round deal the heads to 2 or 4 slices, where their
+// query buffers fit; those take at most 64 rows, so more rows are several
+// chunks then (84 rows, 32 / 8 heads of 64, 6138 keys: 177 us as one chunk of
+// 128 rows, 83 as two).  fp32 rows are several chunks too: the matrix
+// instructions bound them, and a chunk of 128 multiplies the padding of 68 rows
+// (28 / 4 heads of 128, 45450 keys: 1040 us, as two chunks 774).
+StrmSoftPlan plan_strm_soft(int64_t n_vis, int H, int64_t head_bytes, bool f32, int rows, int cus) {
+  StrmSoftPlan p{0, 0, 0};
+  const int64_t tiles = (n_vis + 15) / 16;
+  if (tiles <= 0 || head_bytes % kSegBytes != 0) return p;
+  const auto fits = [&](int qb, int ns) {
+    return soft_slots(qb, ns, 0, qb == 1, H, true, false, 2) > 0 && soft_slots(qb, ns, 0, qb == 1, H, false, true, 2) > 0;
+  };
+  p.nwg = (int)std::min<int64_t>(cus, tiles);
+  const int64_t per_cu = (tiles + cus - 1) / cus;
+  p.max_rows = fits(8, 1) ? 128 : (fits(4, 1) ? 64 : (fits(2, 1) ? 32 : (fits(1, 1) ? 16 : 0)));
+  if (per_cu <= 8 || f32) p.max_rows = std::min(p.max_rows, 64);
+  if (!p.max_rows) return p;
   p.NS = 1;
-  for (int ns = P == 1 ? 8 : 2; ns > 1; ns /= 2)
-    if (per_cu <= 16 / ns && nseg % ns == 0 && nseg / ns >= 2 && rows <= max_rows(ns)) {
+  for (int ns = 4; ns > 1; ns /= 2)
+    if (per_cu <= 16 / ns && H % ns == 0 && fits((std::min(rows, p.max_rows) + 15) / 16, ns)) {
       p.NS = ns;
       break;
     }
+  return p;
+}
+
+int launch_strm_soft(const StrmSoftArgs& a, int ns, bool f32, bool prob, hipStream_t s) {
+  return f32 ? launch_soft<float>(a, ns, prob, s) : launch_soft<StrmBf16>(a, ns, prob, s);
+}
+
+// The slices: the least time is one round with every wave at work, so tiles
+// that would not give each of a CU's 8 waves 32 keys split the contraction
+// (16 / NS tiles per CU and round).  A slice keeps at least two segments.
+// Three query terms take at most two slices: their query buffers fill the LDS.
+// Score kernel, 28 heads of 128: 16 x 144 keys 9.3 us (8 slices), 50 x 144 13.9
+// (8), 128 x 256 37.5 (2); the register-fed kernel with its 4, 4 and 1 slices
+// 16.5, 19.6 and 41.6.
+// More slices take fewer rows a launch, so the rest is the fewest microseconds
+// by 6 per launch and, per segment and 32 rows, 0.85 (fp32) or 0.11 (bf16), the
+// MFMAs of a SIMD's two waves (whole calls by the most slices, then by this:
+// bf16, 100 rows x 1887 keys, 16 heads of 128 34.7 -> 26.7; fp32, 83 x 578 50,
+// by the fewest launches 69).
+StrmPlan plan_strm(int64_t tiles, int64_t row_bytes, int P, bool f32, int rows, bool all, int cus) {
+  StrmPlan p{0, 0, 0, false};
+  if (tiles <= 0 || row_bytes % kSegBytes != 0) return p;
+  const int64_t nseg = row_bytes / kSegBytes, per_cu = (tiles + cus - 1) / cus;
+  // fp32 rows that end in 16 past 32: matrix instructions of 16 rows (by the
+  // query's rows, so that they are the same ranked together or alone)
+  p.half = f32 && !all && (rows + 15) / 16 % 2 != 0;
+  auto max_rows = [&](int ns) { return P == 3 ? 64 : (ns == 8 ? 32 : (ns == 4 || p.half ? 64 : 128)); };
+  double best = 0;
+  for (int ns = P == 1 ? 8 : 2; ns > 0; ns /= 2) {
+    if (ns > 1 && (per_cu > 16 / ns || nseg % ns != 0 || nseg / ns < 2)) continue;
+    if (all && rows > max_rows(ns)) continue;
+    const int unit = p.half ? 16 : 32, units = (rows + unit - 1) / unit;
+    const double t = 6.0 * ((rows + max_rows(ns) - 1) / max_rows(ns)) +
+                     (double)(nseg / ns) * units * unit / 32 * (f32 ? 0.85 : 0.11);
+    if (p.NS && t >= best) continue;
+    p.NS = ns;
+    best = t;
+  }
+  if (!p.NS) return p;
   p.max_rows = max_rows(p.NS);
-  if (rows > p.max_rows) p.NS = 0;
   p.nwg = (int)std::min<int64_t>(cus, tiles);
   return p;
 }
 
-int launch_strm(const StrmArgs& a, const StrmPlan& p, int P, int rows, hipStream_t s) {
+int launch_strm(const StrmArgs& a, const StrmPlan& p, bool f32, int P, int rows, hipStream_t s) {
   const int qb = (rows + 15) / 16;
-  if (rows < 1 || rows > p.max_rows || (P != 1 && P != 3))
+  if (rows < 1 || rows > p.max_rows || (P != 1 && (P != 3 || f32)) || (p.half && !f32))
     return set_error(COFIE_EHIP, "streaming score kernel: %d rows, %d terms", rows, P);
-  if (P == 3) {
-    if (p.NS == 2) {
-      if (qb == 1) return launch_qb<1, 3, 2>(a, s);
-      if (qb == 2) return launch_qb<2, 3, 2>(a, s);
-      return qb == 3 ? launch_qb<3, 3, 2>(a, s) : launch_qb<4, 3, 2>(a, s);
-    }
-    if (qb == 1) return launch_qb<1, 3, 1>(a, s);
-    if (qb == 2) return launch_qb<2, 3, 1>(a, s);
-    return qb == 3 ? launch_qb<3, 3, 1>(a, s) : launch_qb<4, 3, 1>(a, s);
+  if (p.half) return launch_one_term<float, true>(a, p.NS, qb, s);
+  if (P == 1)
+    return f32 ? launch_one_term<float, false>(a, p.NS, qb, s) : launch_one_term<StrmBf16, false>(a, p.NS, qb, s);
+  if (p.NS == 2) {
+    if (qb == 1) return launch_qb<StrmBf16, 1, 3, 2>(a, s);
+    if (qb == 2) return launch_qb<StrmBf16, 2, 3, 2>(a, s);
+    return qb == 3 ? launch_qb<StrmBf16, 3, 3, 2>(a, s) : launch_qb<StrmBf16, 4, 3, 2>(a, s);
   }
-  switch (p.NS) {
-    case 8: return qb == 1 ? launch_qb<1, 1, 8>(a, s) : launch_qb<2, 1, 8>(a, s);
-    case 4:
-      if (qb == 1) return launch_qb<1, 1, 4>(a, s);
-      if (qb == 2) return launch_qb<2, 1, 4>(a, s);
-      return qb == 3 ? launch_qb<3, 1, 4>(a, s) : launch_qb<4, 1, 4>(a, s);
-    case 2:
-      if (qb == 1) return launch_qb<1, 1, 2>(a, s);
-      if (qb == 2) return launch_qb<2, 1, 2>(a, s);
-      if (qb == 3) return launch_qb<3, 1, 2>(a, s);
-      return qb == 4 ? launch_qb<4, 1, 2>(a, s) : launch_qb<8, 1, 2>(a, s);
-    default:
-      if (qb == 1) return launch_qb<1, 1, 1>(a, s);
-      if (qb == 2) return launch_qb<2, 1, 1>(a, s);
-      if (qb == 3) return launch_qb<3, 1, 1>(a, s);
-      return qb == 4 ? launch_qb<4, 1, 1>(a, s) : launch_qb<8, 1, 1>(a, s);
-  }
+  if (qb == 1) return launch_qb<StrmBf16, 1, 3, 1>(a, s);
+  if (qb == 2) return launch_qb<StrmBf16, 2, 3, 1>(a, s);
+  return qb == 3 ? launch_qb<StrmBf16, 3, 3, 1>(a, s) : launch_qb<StrmBf16, 4, 3, 1>(a, s);
 }
 
 }  // namespace cofie

@@ -99,6 +99,23 @@ def test_streaming_score_kernel(n_q, H_q, H_kv, d, n_vis):
         clean(dr, "streaming score kernel")
 
 
+@pytest.mark.parametrize("dtype,n_q,H_q,H_kv,d,n_vis", [
+    ("bf16", 20, 8, 8, 128, 500), ("bf16", 33, 28, 28, 64, 9000), ("bf16", 64, 6, 6, 128, 12000),
+    ("bf16", 129, 3, 3, 64, 5000), ("bf16", 16, 2, 2, 64, 70001), ("bf16", 40, 16, 4, 64, 3000),
+    ("bf16", 24, 1, 1, 64, 66000), ("bf16", 16, 740, 740, 64, 40), ("f32", 18, 4, 4, 64, 700), ("f32", 65, 2, 1, 32, 2000),
+    ("bf16", 20, 6, 3, 128, 33000), ("bf16", 33, 7, 1, 64, 33500), ("bf16", 65, 6, 2, 64, 70001), ("bf16", 48, 12, 3, 64, 140000),
+    ("bf16", 130, 5, 1, 128, 66000), ("bf16", 300, 64, 8, 128, 70001),
+    ("bf16", 9, 28, 4, 64, 900), ("bf16", 7, 32, 8, 128, 33000), ("bf16", 12, 6, 2, 64, 33500), ("bf16", 16, 4, 2, 128, 33000),
+    ("f32", 8, 6, 2, 128, 33000), ("f32", 20, 4, 1, 128, 33000), ("f32", 5, 12, 4, 32, 600), ("bf16", 100, 4, 4, 64, 900),
+    ("f32", 9, 8, 8, 32, 900), ("f32", 48, 4, 4, 64, 33001), ("bf16", 12, 4, 4, 64, 34001), ("f32", 128, 2, 2, 32, 34000),
+    ("f32", 130, 2, 1, 32, 70001)])
+@pytest.mark.parametrize("mode", [B.LOGIT, B.SOFTMAX])
+def test_streaming_passes(dtype, n_q, H_q, H_kv, d, n_vis, mode):
+    with B.DryRun() as dr:
+        qer_single(dr, n_q, H_q, H_kv, d, [n_vis - 5, 5], dtype, 2, mode)
+        clean(dr, "streaming passes")
+
+
 # SOFTMAX with grouped bf16 heads of d = 128 (one query) takes the grouped-head
 # kernel: every instance, ragged rows and tiles, fewer tiles than key ranges
 SOFT_GRP = [(48, 28, 4, [222] * 8 + [224]),   # the high-res heads

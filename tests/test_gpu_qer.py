@@ -80,7 +80,7 @@ STRM_EDGES = [(32, 8, 8, 128, 500),       # eight slices, fewer tiles than CUs
               (48, 28, 4, 128, 20000),    # three query terms, two slices
               (50, 8, 2, 64, 70000),      # three terms, one slice, two segments, two rounds
               (70, 4, 1, 128, 300),       # three terms, two chunks
-              (17, 16, 1, 64, 300)]       # one segment: the general score kernel
+              (17, 16, 1, 64, 300)]       # one segment: every round starts its own pipeline
 
 
 @pytest.mark.parametrize("n_q,H_q,H_kv,d,n_vis", STRM_EDGES)
@@ -89,6 +89,62 @@ def test_streaming_score_kernel_edges(n_q, H_q, H_kv, d, n_vis):
     offs = synth.frame_offsets([n_vis // 7] * 6 + [n_vis - 6 * (n_vis // 7)])
     Q, K = synth.random_qk(n_q + n_vis, n_q, n_vis, H_q, H_kv, d, "bf16")
     run_case(Q, K, offs, H_q, H_kv, d, 3, dtype="bf16", regression=True)
+
+
+# fp32 rows: (n_q, H_q, H_kv, d, keys)
+STRM_F32 = [(8, 4, 4, 32, 512),       # four segments, two slices (two segments each)
+            (33, 8, 8, 64, 8191),     # eight slices; rows past one chunk
+            (70, 4, 4, 32, 33000),    # one slice, two rounds
+            (20, 8, 2, 32, 1000),     # folded grouped heads, one term
+            (17, 2, 2, 16, 300),      # one segment: every round starts its own pipeline
+            (128, 2, 2, 32, 34000),   # eight row blocks of one launch
+            (130, 2, 1, 32, 70001)]   # one segment, several rounds, three chunks of 16-row blocks
+
+
+@pytest.mark.parametrize("n_q,H_q,H_kv,d,n_vis", STRM_F32)
+def test_streaming_score_kernel_f32(n_q, H_q, H_kv, d, n_vis):
+    offs = synth.frame_offsets([n_vis // 7] * 6 + [n_vis - 6 * (n_vis // 7)])
+    Q, K = synth.random_qk(n_q + n_vis, n_q, n_vis, H_q, H_kv, d, "f32")
+    run_case(Q, K, offs, H_q, H_kv, d, 3, dtype="f32")
+
+
+# streaming SOFTMAX passes: (dtype, n_q, H_q, H_kv, d, keys)
+STRM_SOFT = [("bf16", 20, 8, 8, 128, 500),      # four head slices, a block of 16 rows past a block of 32
+             ("bf16", 33, 28, 28, 64, 9000),    # 28 heads in four slices of 7, three row blocks
+             ("bf16", 64, 6, 6, 128, 12000),    # two slices of three heads
+             ("bf16", 129, 3, 3, 64, 5000),     # an odd number of heads, two chunks
+             ("bf16", 16, 2, 2, 64, 70001),     # two segments, two rounds
+             ("bf16", 40, 16, 4, 64, 3000),     # grouped heads read their key head's segments again
+             ("bf16", 24, 1, 1, 64, 66000),     # one segment: every round starts its own pipeline
+             ("bf16", 16, 740, 740, 64, 40),    # statistics of more heads than fit LDS
+             ("bf16", 20, 6, 3, 128, 33000), # key segments held for two query heads, three groups
+             ("bf16", 33, 7, 1, 64, 33500),  # one key segment: the pipeline begins again every round
+             ("bf16", 65, 6, 2, 64, 70001),  # two chunks, rounds
+             ("bf16", 48, 12, 3, 64, 140000),  # three key segments over two slots and several rounds
+             ("bf16", 130, 5, 1, 128, 66000),  # eight row blocks: three query slots
+             ("bf16", 9, 28, 4, 64, 900),  # two heads of 7 in a block, four slices
+             ("bf16", 7, 32, 8, 128, 33000),  # two heads of 4 in a block, their key segments held
+             ("bf16", 12, 6, 2, 64, 33500),  # an odd group's last head alone
+             ("bf16", 16, 4, 2, 128, 33000),  # a group of one pair
+             ("f32", 8, 6, 2, 128, 33000),  # four key segments held, odd groups
+             ("f32", 20, 4, 1, 128, 33000),  # four key segments held
+             ("f32", 5, 12, 4, 32, 600),  # pairs in four slices
+             ("bf16", 100, 4, 4, 64, 900),  # few keys: chunks of 64 rows with slices
+             ("f32", 9, 8, 8, 32, 900),      # one block of 16 rows, four slices
+             ("f32", 48, 4, 4, 64, 33001),   # three blocks of 16 rows
+             ("bf16", 12, 4, 4, 64, 34001),
+             ("f32", 18, 4, 4, 64, 700),
+             ("f32", 65, 2, 1, 32, 2000)]
+
+
+@pytest.mark.parametrize("dtype,n_q,H_q,H_kv,d,n_vis", STRM_SOFT)
+@pytest.mark.parametrize("scale", [0.0, 40.0])  # 40: sums against 0 leave the range of fp32
+def test_streaming_softmax_passes(dtype, n_q, H_q, H_kv, d, n_vis, scale):
+    offs = synth.frame_offsets([n_vis // 5] * 4 + [n_vis - 4 * (n_vis // 5)])
+    Q, K = synth.random_qk(n_q + n_vis, n_q, n_vis, H_q, H_kv, d, dtype)
+    if scale and dtype == "f32":
+        pytest.skip("logits of 40 sigma^2 exceed fp32 dot products at 1e-5")
+    run_case(Q, K, offs, H_q, H_kv, d, 2, mode=B.SOFTMAX, scale=scale, dtype=dtype)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

@@ -104,6 +104,14 @@ def test_batched_softmax(dtype, n_queries, n_q, H_q, H_kv, d, n_frames, max_toke
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_queries,max_tokens", [(5, 900),     # 64 rows, then a query whose heads share blocks, two slices
+                                                  (9, 1600)])   # 128 rows, then one such query, key segments held
+def test_batched_softmax_paired_heads(dtype, n_queries, max_tokens):
+    Q, K, offs, nf = make_case(n_queries, n_queries, 16, 8, 2, 64, 48, dtype, max_tokens)
+    run_batched(Q, K, offs, nf, 8, 2, 64, 6, dtype, mode=B.SOFTMAX)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_batched_wide_pass(dtype):
     """128 query rows (four queries of 32) over more tiles than a split would
     take: the score kernel multiplies all of them in one pass over K."""
