@@ -23,10 +23,11 @@
 // S = Q K^T (bf16 32x32x16 MFMA, or four fp32 32x32x2 over the 16 bytes each
 // lane holds; queries as the A operand): a lane holds one key and 16 query
 // rows of a block in registers, so the max over the rows is in registers but
-// for one exchange between the half waves.  fp32 rows that end in 16 past a
-// multiple of 32 take 16x16x4 MFMAs, which bound them (41 rows x 39984 keys of
-// 28 heads of 128: 254 -> 196 us).  The pipeline runs over all rounds of a
-// workgroup's share (NS = 1).
+// for one exchange between the half waves.  Rows that end in 16 past a multiple
+// of 32 take 16-row MFMAs where those, or three query terms' LDS reads, bound
+// them (41 rows x 39984 keys of 28 heads of 128, fp32: 254 -> 196 us; 48 rows x
+// 58800 keys, 28 / 4 heads of 128, bf16: 29.2 -> 27.5).  The pipeline runs over
+// all rounds of a workgroup's share (NS = 1).
 // Measured against keys loaded to registers in operand shape by a lane select
 // and a DPP rotation, queries restaged through registers (28 heads of 128):
 // 32 rows x 32768 keys 41.6 -> 37.5 us (6.3 TB/s), 64 x 46080 75 -> 57 (5.8),
@@ -1182,6 +1183,18 @@ int launch_one_term(const StrmArgs& a, int NS, int qb, hipStream_t s) {
   }
 }
 
+template <bool HB>
+int launch_three_terms(const StrmArgs& a, int NS, int qb, hipStream_t s) {
+  if (NS == 2) {
+    if (qb == 1) return launch_qb<StrmBf16, 1, 3, 2, HB>(a, s);
+    if (qb == 2) return launch_qb<StrmBf16, 2, 3, 2, HB>(a, s);
+    return qb == 3 ? launch_qb<StrmBf16, 3, 3, 2, HB>(a, s) : launch_qb<StrmBf16, 4, 3, 2, HB>(a, s);
+  }
+  if (qb == 1) return launch_qb<StrmBf16, 1, 3, 1, HB>(a, s);
+  if (qb == 2) return launch_qb<StrmBf16, 2, 3, 1, HB>(a, s);
+  return qb == 3 ? launch_qb<StrmBf16, 3, 3, 1, HB>(a, s) : launch_qb<StrmBf16, 4, 3, 1, HB>(a, s);
+}
+
 // Whether ns slices can take whole pairs of heads.
 bool soft_packs(int H, int G, int ns) { return G > 1 && H / G * ((G + 1) / 2) % ns == 0; }
 
@@ -1312,9 +1325,12 @@ StrmPlan plan_strm(int64_t tiles, int64_t row_bytes, int P, bool f32, int rows, 
   StrmPlan p{0, 0, 0, false};
   if (tiles <= 0 || row_bytes % kSegBytes != 0) return p;
   const int64_t nseg = row_bytes / kSegBytes, per_cu = (tiles + cus - 1) / cus;
-  // fp32 rows that end in 16 past 32: matrix instructions of 16 rows (by the
-  // query's rows, so that they are the same ranked together or alone)
-  p.half = f32 && !all && (rows + 15) / 16 % 2 != 0;
+  // fp32 rows, and three terms, that end in 16 past 32: matrix instructions of
+  // 16 rows (by the query's rows, so that they are the same ranked together or
+  // alone; bf16 rows of one term are HBM-bound and gain nothing, nor do three
+  // terms over few keys, where the launches bound the call: 34 rows x 4104 keys,
+  // 16 / 2 heads of 128 16.2 us both; 4 x 6156, 32 / 8 of 128 19.9 -> 18.9)
+  p.half = !all && (f32 || (P == 3 && tiles * 16 * row_bytes >= 4 << 20)) && (rows + 15) / 16 % 2 != 0;
   auto max_rows = [&](int ns) { return P == 3 ? 64 : (ns == 8 ? 32 : (ns == 4 || p.half ? 64 : 128)); };
   double best = 0;
   for (int ns = P == 1 ? 8 : 2; ns > 0; ns /= 2) {
@@ -1335,19 +1351,11 @@ StrmPlan plan_strm(int64_t tiles, int64_t row_bytes, int P, bool f32, int rows, 
 
 int launch_strm(const StrmArgs& a, const StrmPlan& p, bool f32, int P, int rows, hipStream_t s) {
   const int qb = (rows + 15) / 16;
-  if (rows < 1 || rows > p.max_rows || (P != 1 && (P != 3 || f32)) || (p.half && !f32))
+  if (rows < 1 || rows > p.max_rows || (P != 1 && (P != 3 || f32)))
     return set_error(COFIE_EHIP, "streaming score kernel: %d rows, %d terms", rows, P);
+  if (P == 3) return p.half ? launch_three_terms<true>(a, p.NS, qb, s) : launch_three_terms<false>(a, p.NS, qb, s);
   if (p.half) return launch_one_term<float, true>(a, p.NS, qb, s);
-  if (P == 1)
-    return f32 ? launch_one_term<float, false>(a, p.NS, qb, s) : launch_one_term<StrmBf16, false>(a, p.NS, qb, s);
-  if (p.NS == 2) {
-    if (qb == 1) return launch_qb<StrmBf16, 1, 3, 2>(a, s);
-    if (qb == 2) return launch_qb<StrmBf16, 2, 3, 2>(a, s);
-    return qb == 3 ? launch_qb<StrmBf16, 3, 3, 2>(a, s) : launch_qb<StrmBf16, 4, 3, 2>(a, s);
-  }
-  if (qb == 1) return launch_qb<StrmBf16, 1, 3, 1>(a, s);
-  if (qb == 2) return launch_qb<StrmBf16, 2, 3, 1>(a, s);
-  return qb == 3 ? launch_qb<StrmBf16, 3, 3, 1>(a, s) : launch_qb<StrmBf16, 4, 3, 1>(a, s);
+  return f32 ? launch_one_term<float, false>(a, p.NS, qb, s) : launch_one_term<StrmBf16, false>(a, p.NS, qb, s);
 }
 
 }  // namespace cofie

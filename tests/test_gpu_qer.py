@@ -80,6 +80,7 @@ STRM_EDGES = [(32, 8, 8, 128, 500),       # eight slices, fewer tiles than CUs
               (48, 28, 4, 128, 20000),    # three query terms, two slices
               (50, 8, 2, 64, 70000),      # three terms, one slice, two segments, two rounds
               (70, 4, 1, 128, 300),       # three terms, two chunks
+              (16, 28, 4, 128, 33001),    # three terms, one block of 16 rows, one slice
               (17, 16, 1, 64, 300)]       # one segment: every round starts its own pipeline
 
 
