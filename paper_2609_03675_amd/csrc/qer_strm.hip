@@ -203,6 +203,16 @@ __host__ __device__ __forceinline__ int strm_pair_seg(int v, int second, int sph
   return ((pair / Gp) * G + (g < G ? g : G - 1)) * sph + v % sph;
 }
 
+// Descriptor s of the table, by scalar loads: a vector load's wait would be one
+// for all DMA in flight.
+__device__ __forceinline__ QerStreamDesc strm_seq(const QerStreamDesc* seq, int s) {
+  typedef int i32x8 __attribute__((ext_vector_type(8), aligned(8)));
+  static_assert(sizeof(QerStreamDesc) == sizeof(i32x8), "one load");
+  typedef const __attribute__((address_space(4))) i32x8 const_x8;
+  const uint64_t p = (uint64_t)(seq + __builtin_amdgcn_readfirstlane(s));
+  return __builtin_bit_cast(QerStreamDesc, *(const_x8*)p);
+}
+
 // A wave-uniform value in scalar registers (the loop state that forms it looks
 // divergent to the compiler).
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -309,7 +319,7 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
   };
   auto seek = [&](Rnd& x, int s) __attribute__((always_inline)) {  // the first round of sequence s or later
     for (x.s = s, x.r = 0; x.s < a.n_seq; ++x.s) {
-      x.sd = a.seq ? a.seq[x.s] : a.one;
+      x.sd = a.seq ? strm_seq(a.seq, x.s) : a.one;
       if (x.sd.tile0 >= f_end) {
         x.s = a.n_seq;
         break;
@@ -513,7 +523,7 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
 // Per score one FMA, one v_exp_f32 and one add: a third of the pass's memory
 // time at 64 rows, hidden behind it.  Whole calls, against passes that held
 // statistics per wave and took the keys to registers in operand shape (bf16
-// rows x keys, query / key heads): 64 x 46080, 28 of 128 191 -> 172 us; 32 x
+// rows x keys, query / key heads): 64 x 46080, 28 of 128 191 -> 164 us; 32 x
 // 32768, 28 of 128 115 -> 96; 128 x 50176 374 -> 270; 32 x 2304 92 -> 44; 40 x
 // 65536, 32 / 8 of 128 158 -> 158 (reading the keys again for each query head:
 // 201); 10 x 34788, 32 / 8 of 128 111 -> 88 (heads not paired: 118); fp32, 56 x
@@ -705,7 +715,12 @@ __global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a)
           float2* const mem = a.stats_part + ((row >> 4) * a.nparts + wg) * 16 + (row & 15);
           float2 t = make_float2(-INFINITY, 0.f);  // of the rounds before
           if (!a.direct) t = table[h * ROWS + q];
-          else if (pend_round > 0 && q < a.n_q) t = *mem;
+          else if (pend_round > 0 && q < a.n_q) {
+            t = *mem;
+            // (used here, so that the wait for it -- and with it for all DMA
+            // in flight -- stays in this branch)
+            asm volatile("" : "+v"(t.x), "+v"(t.y));
+          }
           float2 v[KG];
 #pragma unroll
           for (int w = 0; w < KG; ++w) v[w] = p[w * NS * PAIRS + i];
