@@ -265,6 +265,25 @@ __device__ __forceinline__ void wait_counted(int n) {
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Sum and max over the N (2, 4, 8) consecutive lanes of a group.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+template <int N>
+__device__ __forceinline__ float lanes_sum(float v) {
+  v += dpp<0xB1>(v);                          // quad_perm [1,0,3,2]
+  if constexpr (N >= 4) v += dpp<0x4E>(v);    // quad_perm [2,3,0,1]
+  if constexpr (N >= 8) v += dpp<0x141>(v);   // row_half_mirror
+  return v;
+}
+template <int N>
+__device__ __forceinline__ float lanes_max(float v) {
+  v = fmaxf(v, dpp<0xB1>(v));
+  if constexpr (N >= 4) v = fmaxf(v, dpp<0x4E>(v));
+  if constexpr (N >= 8) v = fmaxf(v, dpp<0x141>(v));
+  return v;
+}
 __device__ __forceinline__ float sum_x32(float v) {
   const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
@@ -523,17 +542,21 @@ __global__ __launch_bounds__(kThreads) void qer_strm_kernel(StrmArgs a) {
 // Per score one FMA, one v_exp_f32 and one add: a third of the pass's memory
 // time at 64 rows, hidden behind it.  Whole calls, against passes that held
 // statistics per wave and took the keys to registers in operand shape (bf16
-// rows x keys, query / key heads): 64 x 46080, 28 of 128 191 -> 164 us; 32 x
+// rows x keys, query / key heads): 64 x 46080, 28 of 128 191 -> 159 us; 32 x
 // 32768, 28 of 128 115 -> 96; 128 x 50176 374 -> 270; 32 x 2304 92 -> 44; 40 x
 // 65536, 32 / 8 of 128 158 -> 158 (reading the keys again for each query head:
 // 201); 10 x 34788, 32 / 8 of 128 111 -> 88 (heads not paired: 118); fp32, 56 x
 // 11050, 28 of 128 360 -> 162.
 //  pass 1 (PROB = false): the row's sum of exp2(s c2) over the wave's keys
 //   against 0; rows whose sum leaves (2^-64, 2^64) or that see no key are
-//   summed again against their max.  The waves' pairs meet in LDS, where one
-//   wave (in turn) adds them in wave order a segment later to the workgroup's
-//   table of heads and rows, written to memory once at the end: one pair per
-//   row and workgroup.  (A store per head inside the loop is one more
+//   summed again against their max.  The waves' pairs meet in LDS, where a
+//   segment later they are added to the workgroup's table of heads and rows,
+//   written to memory once at the end: one pair per row and workgroup.  Every
+//   wave adds its share of the rows, a lane a pair, a tree over the lanes of a
+//   row (one wave in turn kept the others waiting: 64 rows x 46080 keys, 28
+//   heads 81 -> 78 us for the pass, fp32 7 rows x 44503, 16 / 2 heads 126 -> 120
+//   a call); with slices, one wave in turn a row a lane, which is shorter work
+//   in all and no longer a wait there (all waves: up to 2 % slower).  (A store per head inside the loop is one more
 //   operation that the in-order wait for the next segment's DMA counts, which
 //   then waits for the segment after: 1.3 us a head.  Only where the table
 //   does not fit LDS -- hundreds of heads -- do the pairs go to memory there.)
@@ -555,6 +578,7 @@ __global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a)
   constexpr int QT = HB ? QB : (QB + 1) / 2, ROWS = 16 * QB, EL = Tile<HB>::EL, BR = Tile<HB>::ROWS;
   constexpr int QBB = PK ? 2 : QB, PAIRS = 16 * QBB;  // query blocks in LDS; statistics pairs of a step and wave
   constexpr int KG = kWaves / NS, CAP = 2 * KG;
+  constexpr bool SHARED = NS == 1;  // pass 1: all waves add a head's pairs, or one in turn
   constexpr int QI = NS * QBB * 2, QW = (QI + kWaves - 1) / kWaves;
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, l = tid & 63;
@@ -564,7 +588,7 @@ __global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a)
   const int slots = KS ? a.slots : SL;
   char* const klds = lds + slots * strm_q_bytes(QBB, 1, NS) + wave * soft_key_slots(SL, KS) * kKeyBytes;
   // past the buffers: pass 2's row constants L [H][ROWS]; pass 1's table
-  // [H][ROWS] of the workgroup's pairs, then the waves' pairs [2][8][PAIRS]
+  // [H][ROWS] of the workgroup's pairs, then the waves' pairs [2][PAIRS][KG] (SHARED) or [2][8][PAIRS]
   float* const lsh = reinterpret_cast<float*>(lds + soft_ring(QB, NS, slots, KS, PK));
   float2* const table = reinterpret_cast<float2*>(lsh);
   float2* const red = table + (PROB || a.direct ? 0 : a.H * ROWS);
@@ -706,7 +730,43 @@ __global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a)
   };
   auto add_pairs = [&]() __attribute__((always_inline)) {
     if (!PROB && pend >= 0) {
-      if (grp == pend % KG) {
+      if constexpr (SHARED) {
+        const float2* p = red + (par ^ 1) * KG * PAIRS;
+#pragma unroll
+        for (int j = 0; j < (PAIRS + 63) / 64; ++j) {
+          const int i = l + 64 * j, row = grp * (PAIRS / KG) + i / KG;
+          const int h = head_of(pend, PK && row >= 16), q = PK ? row & 15 : row;
+          if (i >= PAIRS || h < 0) continue;
+          const float2 v = p[row * KG + i % KG];
+          const bool some = v.y > 0.f;
+          float M = some ? v.x : -INFINITY, Z = some ? v.y : 0.f;
+          const float own = M;
+          M = lanes_max<KG>(M);
+          // (all against 0, as nearly always: nothing to scale)
+          if (some && (own != 0.f || M != 0.f)) Z *= __expf(own - M);
+          Z = lanes_sum<KG>(Z);
+          if (i % KG != 0) continue;
+          const int64_t at = (int64_t)h * a.nq_total + a.q0 + q;
+          float2* const mem = a.stats_part + ((at >> 4) * a.nparts + wg) * 16 + (at & 15);
+          float2 t = make_float2(-INFINITY, 0.f);  // of the rounds before
+          if (!a.direct) {
+            t = table[h * ROWS + q];
+          } else if (pend_round > 0 && q < a.n_q) {
+            t = *mem;
+            // (used here, so that the wait for it -- and with it for all DMA
+            // in flight -- stays in this branch)
+            asm volatile("" : "+v"(t.x), "+v"(t.y));
+          }
+          if (t.y > 0.f) {
+            const float m = fmaxf(M, t.x);
+            if (M != m) Z *= __expf(M - m);  // (M = -inf, Z = 0 if the rows see no key here)
+            Z += t.x != m ? t.y * __expf(t.x - m) : t.y;
+            M = m;
+          }
+          if (!a.direct) table[h * ROWS + q] = make_float2(M, Z);
+          else if (q < a.n_q) *mem = make_float2(M, Z);
+        }
+      } else if (grp == pend % KG) {
         const float2* p = red + (par ^ 1) * kWaves * PAIRS + slice * PAIRS;
         for (int i = l; i < PAIRS; i += 64) {
           const int h = head_of(pend, PK && i >= 16), q = PK ? i & 15 : i;
@@ -791,7 +851,10 @@ __global__ __launch_bounds__(kThreads) void qer_strm_soft_kernel(StrmSoftArgs a)
               z = row_sum(z);
             }
           }
-          if (l < BR) red[(par * kWaves + wave) * PAIRS + BR * qt + l] = make_float2(mx * a.soft_scale, z);
+          const int row = BR * qt + l;  // SHARED: slot grp ^ row % KG of the row's KG (fewer bank conflicts)
+          if (l < BR)
+            red[SHARED ? (par * PAIRS + row) * KG + (grp ^ (row % KG)) : (par * kWaves + wave) * PAIRS + row] =
+                make_float2(mx * a.soft_scale, z);
         }
         acc[qt].clear();
       }
