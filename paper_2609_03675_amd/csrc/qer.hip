@@ -102,7 +102,7 @@ struct Mma<float> {
 // contraction tail shorter than a segment is read in plain MFMA shape.
 //
 // Query fragments.  The contraction is cut into phases of S virtual steps; a
-// phase's query fragments sit in LDS in MFMA operand order ([slice][step]
+// phase's query fragments sit in LDS in MFMA operand order ([step]
 // [term][16-query block][lane], 16 bytes per lane, read by every wave with
 // conflict-free 16-byte LDS loads), double buffered: the fragments of phase
 // i+1 are fetched into registers at the start of phase i and written to LDS
